@@ -62,7 +62,7 @@ struct GemmProb {
   const int32_t* row_model;   // WGRAD of the concatenated first layers: model of each row m (else null)
   // LOGITS with softmax-CE fused (N <= the tile width, so a tile holds whole
   // rows): C/ldc is the gradient dL/dz (storage type) of model `model`, and
-  // the tile's summed row losses go to ce_part[m-tile]. Null: C is the fp32
+  // the summed losses of every CE_ROWS rows go to ce_part[row / CE_ROWS]. Null: C is the fp32
   // logits and a separate CE pass follows.
   float* ce_part;
   // labels of the fused softmax-CE: labels + lab_shared (the model's input
@@ -225,7 +225,7 @@ struct CeProb {
   int64_t ldg;
   int32_t C;
   int32_t model;
-  int32_t nchunks;            // loss partials of this model (row chunks or GEMM m-tiles)
+  int32_t nchunks;            // loss partials of this model (CE_ROWS rows each)
   int32_t B;                  // the model's batch (its input group's)
   int32_t lab_shared, lab_own;  // its labels: labels + lab_shared (group row) or + lab_own (own row)
   // split-K logits (nparts > 0): the logits are the partials parts[s][b][c]
@@ -236,6 +236,17 @@ struct CeProb {
   int32_t nparts;
   const float* bias;
 };
+
+// The per-model loss sum: partials of model m at partial + m * pstride, the
+// losses in host memory. It runs in the workgroup of the first backward GEMM
+// launch whose tile map entry names problem TILE_CE_FINISH.
+struct CeFinish {
+  const CeProb* probs;
+  const float* partial;
+  float* losses;
+  int32_t pstride, nprobs;
+};
+constexpr int TILE_CE_FINISH = -2;
 
 // ---------------------------------------------------------------------------
 // Multi-tensor SGD over 64x64 tiles of every parameter tensor:
@@ -260,7 +271,7 @@ struct SgdTensor {
 // Kernel launch wrappers (kernels.hip). `bf16` selects the storage type.
 // `tile_map` holds one (problem index, tile index within the problem) pair of
 // int32 per workgroup, in launch order; a pair with problem -1 is padding and
-// its workgroup does nothing.
+// its workgroup does nothing, one with TILE_CE_FINISH (GEMM) sums the losses.
 // Learning rates: `lr` for every model, or per model lrv[model] when lrv is
 // not null (device array). Labels: labels[b] for every model, or
 // labels[model * B + b] when per_model_labels is set.
@@ -276,7 +287,7 @@ struct SgdTensor {
 // same layout.
 hipError_t launch_gemm(bool bf16, bool bwd, const GemmProb* probs, const int32_t* tile_map, int ntiles, float lr,
                        const float* lrv, const OptHp* opt, bool keep_grads, const int32_t* labels,
-                       bool per_model_labels, int64_t wsoff, hipStream_t s);
+                       bool per_model_labels, int64_t wsoff, const CeFinish& fin, hipStream_t s);
 hipError_t launch_conv_fwd(bool bf16, const ConvProb* probs, const int32_t* tile_map, int ntiles,
                            hipStream_t s);
 hipError_t launch_conv_dgrad(bool bf16, const ConvProb* probs, const int32_t* tile_map, int ntiles,
@@ -294,14 +305,13 @@ hipError_t launch_set_values(float* dst, const float* vals, int n, hipStream_t s
 // tile_map: one (problem, sample) pair per workgroup.
 hipError_t launch_attn(bool bf16, bool bwd, const AttnProb* probs, const int32_t* tile_map, int nblocks,
                        size_t lds_bytes, hipStream_t s);
-// probs: the first nrows problems need the row pass (their CE is not fused
-// into the logits GEMM); the loss of every one of the nprobs is finished.
-// Partials of model m are at partial + m * pstride; maxB is the largest
-// batch of the problems (each has its own, CeProb::B).
-// Split-K logit partials (CeProb::parts) are read at parts + wsoff bytes.
-hipError_t launch_ce(bool bf16, const CeProb* probs, int nprobs, int nrows, const int32_t* labels,
-                     bool per_model_labels, int maxB, float* partial, int pstride, float* losses, int64_t wsoff,
-                     hipStream_t s);
+// The softmax-CE row pass of the first nrows problems (those whose CE is not
+// fused into the logits GEMM). Partials of model m are at partial + m *
+// pstride; maxB is the largest batch of the problems (each has its own,
+// CeProb::B). Split-K logit partials (CeProb::parts) are read at parts + wsoff
+// bytes.
+hipError_t launch_ce(bool bf16, const CeProb* probs, int nrows, const int32_t* labels, bool per_model_labels, int maxB,
+                     float* partial, int pstride, int64_t wsoff, hipStream_t s);
 // The launch covers tiles [blk0, blk0 + ntiles) of the tile table.
 hipError_t launch_sgd(bool bf16, const SgdTensor* t, const int32_t* tile_tensor, int blk0, int ntiles, float lr,
                       bool use_grad, hipStream_t s);

@@ -1364,14 +1364,16 @@ __device__ __forceinline__ void store_rows(const float* sC, OT* C, int64_t ldc, 
 // Softmax cross-entropy of a logits tile staged in LDS (whole rows: N <= BN),
 // fused into the logits GEMM: CE_LANES lanes per row reduce max and sum with
 // lane shuffles in the same order as ce_rows_kernel, write dL/dz =
-// (softmax - onehot) / B to C, and the row losses of the tile are summed in
-// row order into ce_part[tm] (a workspace buffer: wsoff bytes added).
+// (softmax - onehot) / B to C, and the row losses are summed in row order per
+// CE_ROWS rows into ce_part (a workspace buffer: wsoff bytes added), as
+// ce_rows_kernel does: the partials do not depend on the tile's height, and a
+// lane sums 32 rows instead of one lane all 128 of the tile.
 template <typename T, int BM, int CLD, int NT>
-__device__ __forceinline__ void fused_softmax_ce(float* sC, const GemmProb& p, int m0, int tm,
+__device__ __forceinline__ void fused_softmax_ce(float* sC, const GemmProb& p, int m0,
                                                  const int32_t* __restrict__ labels, int per_model_labels,
                                                  int64_t wsoff) {
   constexpr int RPP = NT / CE_LANES;  // rows per pass
-  static_assert(NT % CE_LANES == 0 && BM % RPP == 0, "whole rows per pass");
+  static_assert(NT % CE_LANES == 0 && BM % RPP == 0 && BM % CE_ROWS == 0, "whole rows per pass, whole partials per tile");
   __shared__ float s_loss[BM];
   const int sub = threadIdx.x % CE_LANES, C = p.N;
   const float invB = 1.0f / (float)p.M;
@@ -1412,11 +1414,33 @@ __device__ __forceinline__ void fused_softmax_ce(float* sC, const GemmProb& p, i
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const int nrows = min(BM, p.M - m0);
+  const int r0 = (int)threadIdx.x * CE_ROWS;
+  if (r0 < BM && m0 + r0 < p.M) {
     float t = 0.f;
-    for (int r = 0; r < nrows; ++r) t += s_loss[r];
-    ((float*)((char*)p.ce_part + wsoff))[tm] = t;
+#pragma unroll
+    for (int r = 0; r < CE_ROWS; ++r) t += s_loss[r0 + r];  // rows past the last one hold 0
+    ((float*)((char*)p.ce_part + wsoff))[(m0 + r0) / CE_ROWS] = t;
+  }
+}
+
+// The loss of each problem of the list (the active models): its row partials
+// added in order (eight loads in flight), times 1 / B, to that model's slot
+// of the host-visible losses. One lane per problem.
+__device__ __forceinline__ void ce_finish(const CeFinish& f, int lane, int nlanes) {
+  for (int i = lane; i < f.nprobs; i += nlanes) {
+    const CeProb& p = f.probs[i];
+    const float* part = f.partial + (int64_t)p.model * f.pstride;
+    const int n = p.nchunks;
+    float s = 0.f;
+    for (int k = 0; k < n; k += 8) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = k + u < n ? part[k + u] : 0.f;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    // the losses are host memory: written through to the system
+    __hip_atomic_store(f.losses + p.model, s * (1.0f / (float)p.B), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -1431,12 +1455,18 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
                                                    const int32_t* __restrict__ tile_map, float lr,
                                                    const float* __restrict__ lrv, const OptHp* __restrict__ opt,
                                                    int keep_grads, const int32_t* __restrict__ labels,
-                                                   int per_model_labels, int64_t wsoff) {
+                                                   int per_model_labels, int64_t wsoff, CeFinish fin) {
   using TL = Tile<T, BM, BN, BK>;
   using SM = Smem<T, BM, BN, BK>;
   __shared__ __attribute__((aligned(16))) char smem[SM::BYTES];
   const int prob = tile_map[2 * blockIdx.x], local = tile_map[2 * blockIdx.x + 1];
-  if (prob < 0) return;  // padding of the XCD-ordered tile list
+  if (prob < 0) {
+    // the loss sum rides in the first backward launch (8 fp32 MLPs of 784
+    // inputs at batch 256: 106.3 us per step with a launch of its own, 104.6
+    // without); else padding of the XCD-ordered tile list
+    if (BWD && prob == TILE_CE_FINISH) ce_finish(fin, threadIdx.x, blockDim.x);
+    return;
+  }
   const GemmProb& p = probs[prob];
   const int tiles_m = (p.M + BM - 1) / BM;
   int split = 0, tile = local;
@@ -1555,7 +1585,7 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
   }
   if (epi != EPI_WGRAD) {
     if (!BWD && epi == EPI_LOGITS && p.ce_part) {
-      fused_softmax_ce<T, BM, CLD, NT>(sC, p, m0, tm, labels, per_model_labels, wsoff);
+      fused_softmax_ce<T, BM, CLD, NT>(sC, p, m0, labels, per_model_labels, wsoff);
       return;
     }
     // Row pass: C[m][n] in 16-byte chunks along n (data gradient: with the
@@ -2888,7 +2918,7 @@ __device__ __forceinline__ float wave_sum(float v) {
 // classes strided over the row's lanes; max and sum over the row by a fixed
 // butterfly of lane shuffles. dz = (softmax - onehot)/B goes to G. Each
 // block sums its rows' losses in row order into partial[model][chunk];
-// ce_finish_kernel adds the chunks in order. The grid covers the largest
+// ce_finish adds the chunks in order. The grid covers the largest
 // batch; a model's blocks beyond its own batch exit.
 template <typename T>
 __global__ __launch_bounds__(CE_ROWS * CE_LANES) void ce_rows_kernel(const CeProb* __restrict__ probs,
@@ -2945,19 +2975,6 @@ __global__ __launch_bounds__(CE_ROWS * CE_LANES) void ce_rows_kernel(const CePro
     for (int r = 0; r < nrows; ++r) t += rowloss[r];
     partial[(int64_t)p.model * pstride + blockIdx.x] = t;
   }
-}
-
-// One lane per problem of the list (the active models), writing that model's
-// slot: its partials (row chunks, or the m-tiles of its fused logits GEMM)
-// added in order.
-__global__ void ce_finish_kernel(const CeProb* __restrict__ probs, const float* __restrict__ partial, int pstride,
-                                 int nprobs, float* __restrict__ losses) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nprobs) return;
-  const int m = probs[i].model, n = probs[i].nchunks;
-  float s = 0.f;
-  for (int k = 0; k < n; ++k) s += partial[(int64_t)m * pstride + k];
-  losses[m] = s * (1.0f / (float)probs[i].B);
 }
 
 // ---------------------------------------------------------------------------
@@ -3221,11 +3238,11 @@ __global__ __launch_bounds__(256) void load_kernel(const float* __restrict__ x, 
 // ---------------------------------------------------------------------------
 hipError_t launch_gemm(bool bf16, bool bwd, const GemmProb* probs, const int32_t* tile_map, int ntiles, float lr,
                        const float* lrv, const OptHp* opt, bool keep_grads, const int32_t* labels,
-                       bool per_model_labels, int64_t wsoff, hipStream_t s) {
+                       bool per_model_labels, int64_t wsoff, const CeFinish& fin, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   auto go = [&](auto kern, int nt) {
     hipLaunchKernelGGL(kern, dim3(ntiles), dim3(nt), 0, s, probs, tile_map, lr, lrv, opt, (int)keep_grads, labels,
-                       (int)per_model_labels, wsoff);
+                       (int)per_model_labels, wsoff, fin);
   };
   if (bf16) {
     constexpr int NT = GemmMma<bf16_t, GEMM_BM_BF16, GEMM_BN_BF16, GEMM_BK_BF16>::NT;
@@ -3394,21 +3411,16 @@ hipError_t launch_attn(bool bf16, bool bwd, const AttnProb* probs, const int32_t
   return hipGetLastError();
 }
 
-hipError_t launch_ce(bool bf16, const CeProb* probs, int nprobs, int nrows, const int32_t* labels,
-                     bool per_model_labels, int maxB, float* partial, int pstride, float* losses, int64_t wsoff,
-                     hipStream_t s) {
-  if (nprobs <= 0) return hipSuccess;
+hipError_t launch_ce(bool bf16, const CeProb* probs, int nrows, const int32_t* labels, bool per_model_labels, int maxB,
+                     float* partial, int pstride, int64_t wsoff, hipStream_t s) {
+  if (nrows <= 0) return hipSuccess;
   const int nchunks = (maxB + CE_ROWS - 1) / CE_ROWS;
-  if (nrows > 0) {
-    if (bf16)
-      hipLaunchKernelGGL(ce_rows_kernel<bf16_t>, dim3(nchunks, nrows), dim3(CE_ROWS * CE_LANES), 0, s, probs, labels,
-                         (int)per_model_labels, partial, pstride, wsoff);
-    else
-      hipLaunchKernelGGL(ce_rows_kernel<float>, dim3(nchunks, nrows), dim3(CE_ROWS * CE_LANES), 0, s, probs, labels,
-                         (int)per_model_labels, partial, pstride, wsoff);
-  }
-  hipLaunchKernelGGL(ce_finish_kernel, dim3((nprobs + 63) / 64), dim3(64), 0, s, probs, partial, pstride, nprobs,
-                     losses);
+  if (bf16)
+    hipLaunchKernelGGL(ce_rows_kernel<bf16_t>, dim3(nchunks, nrows), dim3(CE_ROWS * CE_LANES), 0, s, probs, labels,
+                       (int)per_model_labels, partial, pstride, wsoff);
+  else
+    hipLaunchKernelGGL(ce_rows_kernel<float>, dim3(nchunks, nrows), dim3(CE_ROWS * CE_LANES), 0, s, probs, labels,
+                       (int)per_model_labels, partial, pstride, wsoff);
   return hipGetLastError();
 }
 
