@@ -285,8 +285,9 @@ struct SgdTensor {
 // (split-K partials GemmProb::ce_part, ConvProb::ws, ReduceProb::ws), so that
 // one set of tables serves the arena's workspace (0) or another buffer of the
 // same layout.
-hipError_t launch_gemm(bool bf16, bool bwd, const GemmProb* probs, const int32_t* tile_map, int ntiles, float lr,
-                       const float* lrv, const OptHp* opt, bool keep_grads, const int32_t* labels,
+// variant: the launch's tile shape (GemmVariant).
+hipError_t launch_gemm(bool bf16, bool bwd, int variant, const GemmProb* probs, const int32_t* tile_map, int ntiles,
+                       float lr, const float* lrv, const OptHp* opt, bool keep_grads, const int32_t* labels,
                        bool per_model_labels, int64_t wsoff, const CeFinish& fin, hipStream_t s);
 hipError_t launch_conv_fwd(bool bf16, const ConvProb* probs, const int32_t* tile_map, int ntiles,
                            hipStream_t s);
@@ -321,8 +322,15 @@ hipError_t launch_load(bool bf16, const float* x, int B, int C, int H, int W, vo
                        hipStream_t s);
 
 // Tile shapes the planner must agree with.
-constexpr int GEMM_BM_BF16 = 128, GEMM_BN_BF16 = 128;
-constexpr int GEMM_BM_F32 = 64, GEMM_BN_F32 = 64;
+enum GemmVariant : int { GEMM_LARGE = 0, GEMM_SMALL = 1, GEMM_WIDE = 2 };
+struct GemmTile {
+  int bm, bn;
+};
+constexpr GemmTile gemm_tile(bool bf16, int variant) {
+  const int u = bf16 ? 64 : 32;
+  return GemmTile{variant == GEMM_LARGE ? 2 * u : u, variant == GEMM_SMALL ? u : 2 * u};
+}
+// k-blocks that a split-K problem's kchunk counts
 constexpr int GEMM_BK_BF16 = 64, GEMM_BK_F32 = 32;
 constexpr int CONV_BM_BF16 = 128, CONV_BN_BF16 = 128, CONV_BK_BF16 = 64;
 constexpr int CONV_BM_F32 = 64, CONV_BN_F32 = 64, CONV_BK_F32 = 32;

@@ -277,6 +277,8 @@ struct GemmMma<bf16_t, BM, BN, BK, WGM_, WGN_> {
   static constexpr int LDK = Tile<bf16_t, BM, BN, BK>::LDK;
   static constexpr int LDR_A = BM + KMAJ_PAD_BF16, LDR_B = BN + KMAJ_PAD_BF16;  // k-major row strides
   static constexpr int CLD = BN + 8;
+  static constexpr int A_ELEMS = BM * LDK > BK * LDR_A ? BM * LDK : BK * LDR_A;  // one stage of either layout
+  static constexpr int B_ELEMS = BN * LDK > BK * LDR_B ? BN * LDK : BK * LDR_B;
   static_assert(BK % 16 == 0, "BK must be a multiple of 16");
   using Acc = f32x16[FM][FN];
   __device__ __forceinline__ static void zero(Acc& acc) {
@@ -351,6 +353,8 @@ struct GemmMma<float, BM, BN, BK, WGM_, WGN_> {
   static constexpr int LDK = TL::LDK;
   static constexpr int LDR_A = BM + KMAJ_PAD_F32, LDR_B = BN + KMAJ_PAD_F32;
   static constexpr int CLD = BN + 4;
+  static constexpr int A_ELEMS = BM * LDK > BK * LDR_A ? BM * LDK : BK * LDR_A;  // one stage of either layout
+  static constexpr int B_ELEMS = BN * LDK > BK * LDR_B ? BN * LDK : BK * LDR_B;
   using Acc = f32x4[TL::FM][TL::FN];
   __device__ __forceinline__ static void zero(Acc& acc) {
 #pragma unroll
@@ -414,8 +418,7 @@ struct NoTail {
 
 template <typename T, int BM, int BN, int BK, int DEPTH, class MM, int AM, int BMODE, class LA, class LB, class Tail>
 __device__ __forceinline__ void gemm_loop(LA& la, LB& lb, int nkb, T* smem, typename MM::Acc& acc, Tail&& tail) {
-  using TL = Tile<T, BM, BN, BK>;
-  constexpr int STAGE = TL::A_ELEMS + TL::B_ELEMS;
+  constexpr int STAGE = MM::A_ELEMS + MM::B_ELEMS;
   static_assert(DEPTH >= 1 && DEPTH <= 4, "prefetch depth 1 to 4");
   if (nkb <= 0) {
     tail();
@@ -433,7 +436,7 @@ __device__ __forceinline__ void gemm_loop(LA& la, LB& lb, int nkb, T* smem, type
   if constexpr (DEPTH > 2) issue(std::integral_constant<int, 2 % DEPTH>{}, 2);
   if constexpr (DEPTH > 3) issue(std::integral_constant<int, 3 % DEPTH>{}, 3);
   la.template store<0>(smem);
-  lb.template store<0>(smem + TL::A_ELEMS);
+  lb.template store<0>(smem + MM::A_ELEMS);
   __syncthreads();
   // iteration kb (slot S = kb % DEPTH, LDS buffer kb % 2, both compile-time
   // in the unrolled group below): refill slot S with block kb + DEPTH (for
@@ -443,10 +446,10 @@ __device__ __forceinline__ void gemm_loop(LA& la, LB& lb, int nkb, T* smem, type
     constexpr int U = decltype(pos)::value, S = U % DEPTH, N1 = (U + 1) % DEPTH, BUF = U & 1;
     issue(std::integral_constant<int, S>{}, kb + (DEPTH > 1 ? DEPTH : 1));
     const T* st = smem + BUF * STAGE;
-    MM::template block<AM, BMODE>(st, st + TL::A_ELEMS, acc);
+    MM::template block<AM, BMODE>(st, st + MM::A_ELEMS, acc);
     T* d = smem + (BUF ^ 1) * STAGE;
     la.template store<N1>(d);
-    lb.template store<N1>(d + TL::A_ELEMS);
+    lb.template store<N1>(d + MM::A_ELEMS);
     __syncthreads();
   };
   // the last iteration: no block left to load or stage; it starts with the
@@ -456,7 +459,7 @@ __device__ __forceinline__ void gemm_loop(LA& la, LB& lb, int nkb, T* smem, type
     constexpr int BUF = decltype(pos)::value & 1;
     tail();
     const T* st = smem + BUF * STAGE;
-    MM::template block<AM, BMODE>(st, st + TL::A_ELEMS, acc);
+    MM::template block<AM, BMODE>(st, st + MM::A_ELEMS, acc);
     __syncthreads();
   };
   // a group of G iterations: a multiple of DEPTH (slots) and of 2 (buffers)
@@ -1310,7 +1313,11 @@ __device__ __forceinline__ void opt_update4(const OptHp& h, const f32x4& g, f32x
 // of 8 that changes every 8 rows. Groups of 8 (float4 pairs) stay contiguous
 // for the row passes' float4 reads, and the accumulator writes of a wave
 // spread over the banks.
-__device__ __forceinline__ int sc_col(int r, int c) { return c ^ (((r >> 3) & 7) << 3); }
+template <int BN>
+__device__ __forceinline__ int sc_col(int r, int c) {
+  constexpr int M = BN >= 64 ? 7 : BN / 8 - 1;  // stays within the tile's columns
+  return c ^ (((r >> 3) & M) << 3);
+}
 
 // VE consecutive values (one 16-byte vector) as floats.
 template <typename T, int VE> __device__ __forceinline__ void load_chunk_f(const T* src, float (&v)[VE]) {
@@ -1335,7 +1342,7 @@ __device__ __forceinline__ void store_rows(const float* sC, OT* C, int64_t ldc, 
     float v[VE];
 #pragma unroll
     for (int e = 0; e < VE; e += 4) {
-      const f32x4 x = *(const f32x4*)(sC + r * CLD + sc_col(r, cc * VE + e));
+      const f32x4 x = *(const f32x4*)(sC + r * CLD + sc_col<BN>(r, cc * VE + e));
       v[e] = x[0];
       v[e + 1] = x[1];
       v[e + 2] = x[2];
@@ -1368,7 +1375,7 @@ __device__ __forceinline__ void store_rows(const float* sC, OT* C, int64_t ldc, 
 // CE_ROWS rows into ce_part (a workspace buffer: wsoff bytes added), as
 // ce_rows_kernel does: the partials do not depend on the tile's height, and a
 // lane sums 32 rows instead of one lane all 128 of the tile.
-template <typename T, int BM, int CLD, int NT>
+template <typename T, int BM, int BN, int CLD, int NT>
 __device__ __forceinline__ void fused_softmax_ce(float* sC, const GemmProb& p, int m0,
                                                  const int32_t* __restrict__ labels, int per_model_labels,
                                                  int64_t wsoff) {
@@ -1384,7 +1391,7 @@ __device__ __forceinline__ void fused_softmax_ce(float* sC, const GemmProb& p, i
     const float* z = sC + rl * CLD;
     float mx = -INFINITY;
     if (valid)
-      for (int c = sub; c < C; c += CE_LANES) mx = fmaxf(mx, z[sc_col(rl, c)]);
+      for (int c = sub; c < C; c += CE_LANES) mx = fmaxf(mx, z[sc_col<BN>(rl, c)]);
 #pragma unroll
     for (int off = 1; off < CE_LANES; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
     // the exponentials replace the logits in LDS (each lane its own
@@ -1394,10 +1401,10 @@ __device__ __forceinline__ void fused_softmax_ce(float* sC, const GemmProb& p, i
     float zy = 0.f;
     const int yb = valid ? y[b] : 0;
     if (valid) {
-      zy = z[sc_col(rl, yb)];
+      zy = z[sc_col<BN>(rl, yb)];
       for (int c = sub; c < C; c += CE_LANES) {
-        const float e = expf(z[sc_col(rl, c)] - mx);
-        ze[sc_col(rl, c)] = e;
+        const float e = expf(z[sc_col<BN>(rl, c)] - mx);
+        ze[sc_col<BN>(rl, c)] = e;
         sm += e;
       }
     }
@@ -1408,7 +1415,7 @@ __device__ __forceinline__ void fused_softmax_ce(float* sC, const GemmProb& p, i
       const float inv_s = 1.0f / sm;
       T* g = (T*)p.C + (int64_t)b * p.ldc;
       for (int c = sub; c < C; c += CE_LANES)
-        g[c] = TT<T>::from_f((ze[sc_col(rl, c)] * inv_s - (c == yb ? 1.f : 0.f)) * invB);
+        g[c] = TT<T>::from_f((ze[sc_col<BN>(rl, c)] * inv_s - (c == yb ? 1.f : 0.f)) * invB);
     } else if (sub == 0) {
       s_loss[rl] = 0.f;
     }
@@ -1444,21 +1451,52 @@ __device__ __forceinline__ void ce_finish(const CeFinish& f, int lane, int nlane
   }
 }
 
+// Workgroup shapes of the grouped GEMM (tile variants, chosen per launch by the
+// planner). The MFMA form and the order of k are the same in all of them, so
+// an output element's bits do not depend on the variant.
+//   GEMM_LARGE  bf16 128x128 by 16 waves, fp32 64x64 by 4 waves
+//   GEMM_SMALL  bf16 64x64, fp32 32x32, 4 waves each: four times the
+//               workgroups for a launch whose large tiles leave CUs idle
+//   GEMM_WIDE   the small height with the large width, for such a launch with
+//               a fused softmax-CE of more classes than the small width
+// A small tile's loop is bound by the latency of its loads: its loads run four
+// k-blocks ahead (12 bf16 MLPs with Adam 127 us per step, 134 with 128-column
+// k-blocks two ahead; 5 fp32 attention models 143 us, 160 with 64-column
+// blocks two ahead). A large tile has no registers for more than two.
+template <typename T, int VAR> struct GemmVar;
+template <int BM_, int BN_, int BK_, int WGM, int WGN, int DEPTH_, int WPE_, typename T>
+struct GemmShape {
+  static constexpr int BM = BM_, BN = BN_, BK = BK_, DEPTH = DEPTH_, WPE = WPE_;
+  using MM = GemmMma<T, BM, BN, BK, WGM, WGN>;
+  // the double-buffered operand stages, reused by the epilogue's fp32 tile
+  static constexpr size_t MAIN = 2 * (size_t)(MM::A_ELEMS + MM::B_ELEMS) * sizeof(T);
+  static constexpr size_t EPI = (size_t)BM * MM::CLD * sizeof(float);
+  static constexpr size_t BYTES = MAIN > EPI ? MAIN : EPI;
+  static_assert(BM == gemm_tile(sizeof(T) == 2, 0).bm || BM == gemm_tile(sizeof(T) == 2, 1).bm, "planner's tiles");
+};
+template <> struct GemmVar<bf16_t, GEMM_LARGE> : GemmShape<128, 128, 64, UN_GEMM_WGM, UN_GEMM_WGN, UN_GEMM_DEPTH, UN_GEMM_WGM * UN_GEMM_WGN / 2, bf16_t> {};
+template <> struct GemmVar<bf16_t, GEMM_SMALL> : GemmShape<64, 64, 64, 2, 2, 4, 4, bf16_t> {};
+template <> struct GemmVar<bf16_t, GEMM_WIDE> : GemmShape<64, 128, 64, 2, 4, 2, 4, bf16_t> {};
+template <> struct GemmVar<float, GEMM_LARGE> : GemmShape<64, 64, 32, 2, 2, 2, 2, float> {};
+template <> struct GemmVar<float, GEMM_SMALL> : GemmShape<32, 32, 32, 2, 2, 4, 4, float> {};
+template <> struct GemmVar<float, GEMM_WIDE> : GemmShape<32, 64, 32, 2, 2, 4, 4, float> {};
+
 // OPT: the update follows a per-model OptHp (`opt`, not null) instead of
 // fma(-lr, g, w); a separate instantiation, so that plain SGD pays nothing.
 // BWD: the launch's problems are data gradients (A row-major, B k-major) and
 // weight gradients (both k-major), told apart by p.amode; else forward
 // problems (both row-major). Each variant compiles only its own k-loops.
-template <typename T, int BM, int BN, int BK, bool OPT, bool BWD>
-__global__ __launch_bounds__((GemmMma<T, BM, BN, BK>::NT)) __attribute__((amdgpu_waves_per_eu((GemmMma<T, BM, BN, BK>::NT / 128))))
+template <typename T, int VAR, bool OPT, bool BWD>
+__global__ __launch_bounds__((GemmVar<T, VAR>::MM::NT)) __attribute__((amdgpu_waves_per_eu((GemmVar<T, VAR>::WPE))))
 void gemm_kernel(const GemmProb* __restrict__ probs,
                                                    const int32_t* __restrict__ tile_map, float lr,
                                                    const float* __restrict__ lrv, const OptHp* __restrict__ opt,
                                                    int keep_grads, const int32_t* __restrict__ labels,
                                                    int per_model_labels, int64_t wsoff, CeFinish fin) {
-  using TL = Tile<T, BM, BN, BK>;
-  using SM = Smem<T, BM, BN, BK>;
-  __shared__ __attribute__((aligned(16))) char smem[SM::BYTES];
+  using V = GemmVar<T, VAR>;
+  using MM = typename V::MM;
+  constexpr int BM = V::BM, BN = V::BN, BK = V::BK;
+  __shared__ __attribute__((aligned(16))) char smem[V::BYTES];
   const int prob = tile_map[2 * blockIdx.x], local = tile_map[2 * blockIdx.x + 1];
   if (prob < 0) {
     // the loss sum rides in the first backward launch (8 fp32 MLPs of 784
@@ -1477,22 +1515,22 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
   const int tn = tile / tiles_m, tm = tile - tn * tiles_m;   // m fastest: neighbours share B
   const int m0 = tm * BM, n0 = tn * BN;
 
-  using MM = GemmMma<T, BM, BN, BK>;
   typename MM::Acc acc;
   MM::zero(acc);
 
-  constexpr int NT = MM::NT, D = UN_GEMM_DEPTH;
+  constexpr int NT = MM::NT, D = V::DEPTH;
   constexpr int PAD = sizeof(T) == 2 ? KMAJ_PAD_BF16 : KMAJ_PAD_F32;
-  // the k range of this tile: all of K, or the split's chunk (rows kb0 * BK ..)
-  const int kb0 = split * p.kchunk;
-  const int kc = p.epi == EPI_WPART ? min(p.K - kb0 * BK, p.kchunk * BK) : p.K;
+  // the k range of this tile: all of K, or the split's chunk of kchunk k-blocks
+  // (of KB columns, whatever the variant's own) from k0 on
+  constexpr int KB = sizeof(T) == 2 ? GEMM_BK_BF16 : GEMM_BK_F32;
+  const int k0 = split * p.kchunk * KB;
+  const int kc = p.epi == EPI_WPART ? min(p.K - k0, p.kchunk * KB) : p.K;
   const int nkb = (kc + BK - 1) / BK;
   constexpr int CPR = BN / 4, NCH = BM * CPR / NT;  // epilogue float4 chunks per row, per thread
   const int ns = p.nsplit;
   f32x4 w0[NCH];  // master weights of the fused update (weight gradient only)
   if constexpr (!BWD) {
     // row-major operands from column k0 on (a split's chunk, else 0), kc of them
-    const int64_t k0 = (int64_t)kb0 * BK;
     RowLoader<T, BM, BK, NT, D> la;
     RowLoader<T, BN, BK, NT, D> lb;
     la.init((const T*)p.A + (int64_t)m0 * p.lda + k0, p.lda, p.M - m0, kc);
@@ -1517,7 +1555,6 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
     KRowLoader<T, BM, BK, NT, D, PAD> la;
     KRowLoader<T, BN, BK, NT, D, PAD> lb;
     const int bcol = p.nsplit - n0;
-    const int64_t k0 = (int64_t)kb0 * BK;  // k-major: rows k0 .. of both operands
     la.init((const T*)p.A + k0 * p.lda, p.lda, m0, kc, -1);
     lb.init((const T*)p.B + k0 * p.ldb, p.ldb, n0, kc, bcol >= 0 && bcol < BN ? bcol : -1);
     gemm_loop<T, BM, BN, BK, D, MM, OP_KMAJ, OP_KMAJ>(la, lb, nkb, (T*)smem, acc, [&] {
@@ -1546,25 +1583,33 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
   // Epilogue 1: per-element work (bias, ReLU) in registers, then the fp32
   // tile to LDS (rows of CLD floats: float4-aligned).
   constexpr int CLD = MM::CLD;
-  static_assert(CLD <= SM::CLD, "epilogue tile exceeds its LDS");
   float* sC = (float*)smem;
   const int epi = p.epi;
-  MM::for_groups(acc, [&](int rl, int cl, float (&v)[4]) {
-      const int mb = m0 + rl, n = n0 + cl;
-      const int nv = max(0, min(4, p.M - mb));
-      if (n < p.N && nv > 0) {
-        if (epi == EPI_FWD || epi == EPI_LOGITS) {
-          const float b = p.bias[n];
+  const auto stage = [&](int rl, int cl, const float (&v)[4]) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            v[r] += b;
-            if (p.relu && !p.R) v[r] = fmaxf(v[r], 0.f);  // with a skip input: after the sum
-          }
-        }
+    for (int r = 0; r < 4; ++r) sC[(rl + r) * CLD + sc_col<BN>(rl + r, cl)] = v[r];
+  };
+  if (!BWD && epi != EPI_WPART) {
+    // One straight path with the fields as values (read through the problem,
+    // they were loaded and tested again for every element): attn8
+    // 470 -> 437 us per step, resnet8 395 -> 367. Rows past M get a bias that
+    // no store below takes.
+    const gptr<const float> bias = G(p.bias);
+    const int N = p.N;
+    const bool relu = p.relu && !p.R;  // with a skip input: after the sum
+    MM::for_groups(acc, [&](int rl, int cl, float (&v)[4]) {
+      const int n = n0 + cl;
+      const float b = n < N ? bias[n] : 0.f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        v[r] += b;
+        if (relu) v[r] = fmaxf(v[r], 0.f);
       }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) sC[(rl + r) * CLD + sc_col(rl + r, cl)] = v[r];
-  });
+      stage(rl, cl, v);
+    });
+  } else {
+    MM::for_groups(acc, [&](int rl, int cl, float (&v)[4]) { stage(rl, cl, v); });
+  }
   __syncthreads();
 
   if (epi == EPI_WPART) {
@@ -1575,7 +1620,7 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
       const int idx = threadIdx.x + NT * q, r = idx / CPR, cc = idx - r * CPR;
       const int m = m0 + r, n = n0 + cc * 4;
       if (m >= p.M || n >= p.N) continue;
-      const f32x4 g = *(const f32x4*)(sC + r * CLD + sc_col(r, cc * 4));
+      const f32x4 g = *(const f32x4*)(sC + r * CLD + sc_col<BN>(r, cc * 4));
       float* d = ws + (int64_t)m * p.ldws + n;
       if (n + 4 <= p.N) *(gptr<f32x4>)d = g;
       else
@@ -1585,7 +1630,7 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
   }
   if (epi != EPI_WGRAD) {
     if (!BWD && epi == EPI_LOGITS && p.ce_part) {
-      fused_softmax_ce<T, BM, CLD, NT>(sC, p, m0, labels, per_model_labels, wsoff);
+      fused_softmax_ce<T, BM, BN, CLD, NT>(sC, p, m0, labels, per_model_labels, wsoff);
       return;
     }
     // Row pass: C[m][n] in 16-byte chunks along n (data gradient: with the
@@ -1617,7 +1662,7 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
     // this row's model: its own optimizer, or its own rate (staged in s_lr)
     const int mdl = OPT ? (p.row_model ? p.row_model[m] : p.model) : 0;
     const float lr_m = (!OPT && lrv) ? s_lr[r] : lr;
-    float* s = sC + r * CLD + sc_col(r, cc * 4);
+    float* s = sC + r * CLD + sc_col<BN>(r, cc * 4);
     const int64_t base = (int64_t)m * p.ldc + n;
     if (n + 4 <= ns) {
       const f32x4 g = *(const f32x4*)s;
@@ -3236,24 +3281,28 @@ __global__ __launch_bounds__(256) void load_kernel(const float* __restrict__ x, 
 // ---------------------------------------------------------------------------
 // Launch wrappers
 // ---------------------------------------------------------------------------
-hipError_t launch_gemm(bool bf16, bool bwd, const GemmProb* probs, const int32_t* tile_map, int ntiles, float lr,
-                       const float* lrv, const OptHp* opt, bool keep_grads, const int32_t* labels,
+hipError_t launch_gemm(bool bf16, bool bwd, int variant, const GemmProb* probs, const int32_t* tile_map, int ntiles,
+                       float lr, const float* lrv, const OptHp* opt, bool keep_grads, const int32_t* labels,
                        bool per_model_labels, int64_t wsoff, const CeFinish& fin, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   auto go = [&](auto kern, int nt) {
     hipLaunchKernelGGL(kern, dim3(ntiles), dim3(nt), 0, s, probs, tile_map, lr, lrv, opt, (int)keep_grads, labels,
                        (int)per_model_labels, wsoff, fin);
   };
-  if (bf16) {
-    constexpr int NT = GemmMma<bf16_t, GEMM_BM_BF16, GEMM_BN_BF16, GEMM_BK_BF16>::NT;
-    if (!bwd) go(gemm_kernel<bf16_t, GEMM_BM_BF16, GEMM_BN_BF16, GEMM_BK_BF16, false, false>, NT);
-    else if (opt) go(gemm_kernel<bf16_t, GEMM_BM_BF16, GEMM_BN_BF16, GEMM_BK_BF16, true, true>, NT);
-    else go(gemm_kernel<bf16_t, GEMM_BM_BF16, GEMM_BN_BF16, GEMM_BK_BF16, false, true>, NT);
-  } else {
-    if (!bwd) go(gemm_kernel<float, GEMM_BM_F32, GEMM_BN_F32, GEMM_BK_F32, false, false>, 256);
-    else if (opt) go(gemm_kernel<float, GEMM_BM_F32, GEMM_BN_F32, GEMM_BK_F32, true, true>, 256);
-    else go(gemm_kernel<float, GEMM_BM_F32, GEMM_BN_F32, GEMM_BK_F32, false, true>, 256);
-  }
+  auto pass = [&](auto t, auto v) {
+    using T = decltype(t);
+    constexpr int VAR = decltype(v)::value, NT = GemmVar<T, VAR>::MM::NT;
+    if (!bwd) go(gemm_kernel<T, VAR, false, false>, NT);
+    else if (opt) go(gemm_kernel<T, VAR, true, true>, NT);
+    else go(gemm_kernel<T, VAR, false, true>, NT);
+  };
+  auto type = [&](auto t) {
+    if (variant == GEMM_SMALL) pass(t, std::integral_constant<int, GEMM_SMALL>{});
+    else if (variant == GEMM_WIDE) pass(t, std::integral_constant<int, GEMM_WIDE>{});
+    else pass(t, std::integral_constant<int, GEMM_LARGE>{});
+  };
+  if (bf16) type(bf16_t{});
+  else type(float{});
   return hipGetLastError();
 }
 

@@ -38,6 +38,16 @@ using namespace un;
 
 namespace {
 
+// A GEMM launch of at most this many large tiles (one per CU) runs small ones:
+// the launch then lasts as long as one tile's chain of k-blocks, and a small
+// tile's k-block reads a quarter of the LDS bytes and (fp32) runs a quarter of
+// the MFMAs. Steps with large tiles only / with this rule, in us: 2 fp32 MLPs
+// 56.5 / 37.4, 8 fp32 MLPs 103 / 69, 5 fp32 attention models 283 / 143, 12
+// bf16 MLPs with Adam 144 / 127, one bf16 MLP 165 / 141. With the line at 512
+// attn8 goes from 430 to 440 and the 64 MLPs from 769 to 774 us (two small
+// tiles per CU and more re-read operands beat one large one less often).
+constexpr int GEMM_SMALL_MAX = 256;
+
 constexpr size_t NONE = ~(size_t)0;
 
 inline int64_t rup(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
@@ -122,7 +132,7 @@ struct Launch {
   int kclass;
   size_t probs, map;  // arena offsets
   int count;
-  int mode = 0;       // conv weight gradient: code variant (launch_conv_wgrad); CE: problems needing the row pass
+  int mode = 0;       // GEMM: tile variant; conv weight gradient: code variant (launch_conv_wgrad); CE: problems needing the row pass
   size_t lds = 0;     // halo conv: dynamic LDS bytes
 };
 
@@ -725,18 +735,31 @@ static void build_tables(un_ctx* c, Tables& T) {
     return (c->sbase && off != NONE) ? (float*)(c->sbase + off + (size_t)add) : nullptr;
   };
 
-  const int GBM = bf ? GEMM_BM_BF16 : GEMM_BM_F32, GBN = bf ? GEMM_BN_BF16 : GEMM_BN_F32;
   const int CBM = bf ? CONV_BM_BF16 : CONV_BM_F32, CBN = bf ? CONV_BN_BF16 : CONV_BN_F32;
   // softmax-CE is fused into a model's logits GEMM when a tile holds whole
   // rows of logits; the loss partials of model m start at m * ce_pstride
   const int ce_pstride = cdiv(c->maxB, CE_ROWS);
-  auto ce_fused = [&](const Block& b) { return b.kind == 0 && b.N <= GBN && b.fsplits == 0; };
+  auto ce_fused = [&](const Block& b) { return b.kind == 0 && b.N <= gemm_tile(bf, GEMM_LARGE).bn && b.fsplits == 0; };
 
   // Problems of one launch are ordered longest-K first (their tiles are the
   // longest-running), so the ragged tail of a level is made of short tiles.
   // Order affects scheduling only: every tile computes the same values.
   auto emit_gemm = [&](std::vector<GemmProb>& ps, std::vector<Launch>& out, int kclass) {
     if (ps.empty()) return;
+    // Tile variant of the launch. It decides which workgroup computes an
+    // element, never its value, so it may depend on the whole launch.
+    int variant = GEMM_LARGE;
+    {
+      int64_t large = 0;
+      bool wide = false;
+      const GemmTile tl = gemm_tile(bf, GEMM_LARGE);
+      for (const GemmProb& p : ps) {
+        large += (int64_t)cdiv(p.M, tl.bm) * cdiv(p.N, tl.bn) * (p.epi == EPI_WPART ? p.splits : 1);
+        wide = wide || (p.ce_part && p.N > gemm_tile(bf, GEMM_SMALL).bn);
+      }
+      if (large <= GEMM_SMALL_MAX) variant = wide ? GEMM_WIDE : GEMM_SMALL;
+    }
+    const int GBM = gemm_tile(bf, variant).bm, GBN = gemm_tile(bf, variant).bn;
     // k length of one tile: K, or one split's chunk
     const int BKg = bf ? GEMM_BK_BF16 : GEMM_BK_F32;
     auto klen = [&](const GemmProb& x) { return x.epi == EPI_WPART ? std::min(x.K, x.kchunk * BKg) : x.K; };
@@ -825,7 +848,7 @@ static void build_tables(un_ctx* c, Tables& T) {
         fix.push_back(b0 + f);
     }
     size_t mo = put(map.data(), map.size() * 4);
-    out.push_back(Launch{0, kclass, po, mo, (int)(map.size() / 2)});
+    out.push_back(Launch{0, kclass, po, mo, (int)(map.size() / 2), variant});
   };
   auto emit_conv_one = [&](std::vector<ConvProb>& ps, std::vector<Launch>& out, int kind, int kclass) {
     if (ps.empty()) return;
@@ -1652,8 +1675,11 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
   build_tables(c, T);
 
   // --- allocate the arena: buffers + tables (room for the tables of any
-  // active subset, which are never larger than twice the full set's)
-  c->tables_cap = 2 * T.host.size() + ((size_t)1 << 20);
+  // active subset: never larger than twice the full set's, except that a
+  // launch of few enough tiles for the small tiles may come out of a full one
+  // with large tiles: at most 4 x GEMM_SMALL_MAX entries, 4.3 times that with
+  // the XCD padding (one run of 8 among 7 of 1), 8 bytes each)
+  c->tables_cap = 2 * T.host.size() + ((size_t)1 << 20) + (size_t)2 * levels * (18 * GEMM_SMALL_MAX + 64) * 8;
   c->tables_off = A.take(c->tables_cap);
   c->bytes = A.top;
   if (dry) return UN_OK;
@@ -1831,7 +1857,7 @@ static hipError_t run_launch(un_ctx* c, const Launch& l, float lr) {
   float* const ce_part = (float*)((char*)c->at<float>(c->ce_partial) + c->wsoff);  // loss partials
   switch (l.kind) {
     case 0:
-      e = launch_gemm(c->bf16, l.kclass == UN_K_GEMM_BWD, c->at<GemmProb>(l.probs), c->at<int32_t>(l.map), l.count, lr,
+      e = launch_gemm(c->bf16, l.kclass == UN_K_GEMM_BWD, l.mode, c->at<GemmProb>(l.probs), c->at<int32_t>(l.map), l.count, lr,
                       c->lrv, c->optp, c->keep_grads, c->at<int32_t>(c->ydev), c->labels_per_model, c->wsoff,
                       CeFinish{c->at<CeProb>(c->ce.probs), ce_part, c->losses_host, cdiv(c->maxB, CE_ROWS), c->ce.count},
                       c->stream);
