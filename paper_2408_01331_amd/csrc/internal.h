@@ -23,7 +23,8 @@ typedef uint16_t bf16_t;
 //   dgrad    dX[b][i] = sum_o G[b][o] W[o][i]    A = G row-major,  B = W k-major
 //   wgrad    dW[o][i] = sum_b G[b][o] X[b][i]    A = G k-major,    B = X k-major
 // The wgrad's B loader reads 1 in column n == nsplit (for every k < K): that
-// column of the product is the bias gradient sum_b G[b][o].
+// column of the product is the bias gradient sum_b G[b][o]. Where the weight
+// columns fill whole tiles it is summed without a product (bias_tile).
 // ---------------------------------------------------------------------------
 enum OpLayout : int32_t { OP_ROW = 0, OP_KMAJ = 1 };
 
@@ -44,8 +45,10 @@ struct GemmProb {
   int32_t M, N, K;
   int32_t epi, relu;
   int32_t amode, bmode;       // OpLayout of A and B
-  int32_t tiles_n;
+  int32_t tiles_n;            // columns of tiles, the bias tiles' included
   int32_t nsplit;
+  int32_t bias_tile;          // weight gradients: N == nsplit, and one more tile column for the bias
+                              // gradient alone (column sums of A); else 0, N == nsplit + 1
   int32_t model;              // WGRAD: the model whose learning rate applies (single-model problems)
   void* C;                    // WGRAD: gradient dW [m][ldc] (stored only when gradients are kept)
   int64_t ldc;

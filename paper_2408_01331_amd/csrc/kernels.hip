@@ -1451,6 +1451,61 @@ __device__ __forceinline__ void ce_finish(const CeFinish& f, int lane, int nlane
   }
 }
 
+// Bias gradient of a weight-gradient problem whose K is a whole number of
+// small tiles (GemmProb::bias_tile): sum over the tile's k range [k0, k0 + kc)
+// of column m of A = G[k][m], for the BM columns from m0; thread t < BM returns
+// column m0 + t's. As one more product column (the bias column of the other
+// problems) it would need a tile column of its own, with the whole k loop:
+// K = 128 took two tile columns instead of one. This reads A only (attn8, whose
+// widths are 64 and 128: 437 -> 368 us per step; 64 MLPs, whose first layers
+// read 1024 inputs: 775 -> 757).
+// Bound by its loads (four of 16 bytes in flight per thread). The order of the
+// sum does not depend on the tile variant: rows k = r (mod R) in ascending
+// order for each r, then the R partial sums in order of r.
+template <typename T, int BM, int NT>
+__device__ __forceinline__ float bias_sum(const GemmProb& p, int m0, int k0, int kc, float* sm) {
+  constexpr int VEC = TT<T>::VEC, CPR = BM / VEC, RP = NT / CPR, R = sizeof(T) == 2 ? 64 : 32, S = R / RP, U = 4 / S;
+  static_assert(S >= 1 && S * RP == R && U >= 1 && NT >= BM, "whole passes of R rows");
+  const int c = threadIdx.x % CPR, j = threadIdx.x / CPR, ld = (int)p.lda * (int)sizeof(T);
+  // rows past the range (and the last row's columns past the matrix) read zero
+  const __amdgpu_buffer_rsrc_t rs =
+      make_rsrc((const T*)p.A + (int64_t)k0 * p.lda + m0, ((int64_t)kc * p.lda - m0) * (int64_t)sizeof(T));
+  float acc[S][VEC];
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) acc[s][e] = 0.f;
+  for (int k = 0; k < kc; k += U * R) {
+    u32x4 v[U][S];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const int row = k + u * R + s * RP + j;
+        v[u][s] = __builtin_bit_cast(
+            u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, row < kc ? row * ld + c * 16 : 0x7ffffff0, 0, 0));
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[s][e] += vget<T>(v[u][s], e);
+  }
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+#pragma unroll
+    for (int e = 0; e < VEC; e += 4)
+      *(f32x4*)(sm + (s * RP + j) * BM + c * VEC + e) = f32x4{acc[s][e], acc[s][e + 1], acc[s][e + 2], acc[s][e + 3]};
+  __syncthreads();
+  float g = 0.f;
+  if ((int)threadIdx.x < BM) {
+#pragma unroll 16
+    for (int r = 0; r < R; ++r) g += sm[r * BM + threadIdx.x];
+  }
+  return g;
+}
+
 // Workgroup shapes of the grouped GEMM (tile variants, chosen per launch by the
 // planner). The MFMA form and the order of k are the same in all of them, so
 // an output element's bits do not depend on the variant.
@@ -1462,11 +1517,13 @@ __device__ __forceinline__ void ce_finish(const CeFinish& f, int lane, int nlane
 // A small tile's loop is bound by the latency of its loads: its loads run four
 // k-blocks ahead (12 bf16 MLPs with Adam 127 us per step, 134 with 128-column
 // k-blocks two ahead; 5 fp32 attention models 143 us, 160 with 64-column
-// blocks two ahead). A large tile has no registers for more than two.
+// blocks two ahead). A large tile has no registers for more than two, nor has
+// the bf16 backward pass, whose four-deep form spilled (attn8 368 us with two,
+// 383 with three, 388 with four).
 template <typename T, int VAR> struct GemmVar;
-template <int BM_, int BN_, int BK_, int WGM, int WGN, int DEPTH_, int WPE_, typename T>
+template <int BM_, int BN_, int BK_, int WGM, int WGN, int DEPTH_, int DEPTH_BWD_, int WPE_, typename T>
 struct GemmShape {
-  static constexpr int BM = BM_, BN = BN_, BK = BK_, DEPTH = DEPTH_, WPE = WPE_;
+  static constexpr int BM = BM_, BN = BN_, BK = BK_, DEPTH = DEPTH_, DEPTH_BWD = DEPTH_BWD_, WPE = WPE_;
   using MM = GemmMma<T, BM, BN, BK, WGM, WGN>;
   // the double-buffered operand stages, reused by the epilogue's fp32 tile
   static constexpr size_t MAIN = 2 * (size_t)(MM::A_ELEMS + MM::B_ELEMS) * sizeof(T);
@@ -1474,12 +1531,12 @@ struct GemmShape {
   static constexpr size_t BYTES = MAIN > EPI ? MAIN : EPI;
   static_assert(BM == gemm_tile(sizeof(T) == 2, 0).bm || BM == gemm_tile(sizeof(T) == 2, 1).bm, "planner's tiles");
 };
-template <> struct GemmVar<bf16_t, GEMM_LARGE> : GemmShape<128, 128, 64, UN_GEMM_WGM, UN_GEMM_WGN, UN_GEMM_DEPTH, UN_GEMM_WGM * UN_GEMM_WGN / 2, bf16_t> {};
-template <> struct GemmVar<bf16_t, GEMM_SMALL> : GemmShape<64, 64, 64, 2, 2, 4, 4, bf16_t> {};
-template <> struct GemmVar<bf16_t, GEMM_WIDE> : GemmShape<64, 128, 64, 2, 4, 2, 4, bf16_t> {};
-template <> struct GemmVar<float, GEMM_LARGE> : GemmShape<64, 64, 32, 2, 2, 2, 2, float> {};
-template <> struct GemmVar<float, GEMM_SMALL> : GemmShape<32, 32, 32, 2, 2, 4, 4, float> {};
-template <> struct GemmVar<float, GEMM_WIDE> : GemmShape<32, 64, 32, 2, 2, 4, 4, float> {};
+template <> struct GemmVar<bf16_t, GEMM_LARGE> : GemmShape<128, 128, 64, UN_GEMM_WGM, UN_GEMM_WGN, UN_GEMM_DEPTH, UN_GEMM_DEPTH, UN_GEMM_WGM * UN_GEMM_WGN / 2, bf16_t> {};
+template <> struct GemmVar<bf16_t, GEMM_SMALL> : GemmShape<64, 64, 64, 2, 2, 4, 2, 4, bf16_t> {};
+template <> struct GemmVar<bf16_t, GEMM_WIDE> : GemmShape<64, 128, 64, 2, 4, 2, 2, 4, bf16_t> {};
+template <> struct GemmVar<float, GEMM_LARGE> : GemmShape<64, 64, 32, 2, 2, 2, 2, 2, float> {};
+template <> struct GemmVar<float, GEMM_SMALL> : GemmShape<32, 32, 32, 2, 2, 4, 4, 4, float> {};
+template <> struct GemmVar<float, GEMM_WIDE> : GemmShape<32, 64, 32, 2, 2, 4, 4, 4, float> {};
 
 // OPT: the update follows a per-model OptHp (`opt`, not null) instead of
 // fma(-lr, g, w); a separate instantiation, so that plain SGD pays nothing.
@@ -1518,7 +1575,27 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
   typename MM::Acc acc;
   MM::zero(acc);
 
-  constexpr int NT = MM::NT, D = V::DEPTH;
+  constexpr int NT = MM::NT, D = BWD ? V::DEPTH_BWD : V::DEPTH;
+  if constexpr (BWD) {
+    if (p.bias_tile && tn == p.tiles_n - 1) {
+      // the last tile column: the bias gradient alone, and its update
+      constexpr int KB = sizeof(T) == 2 ? GEMM_BK_BF16 : GEMM_BK_F32;
+      const int kb = split * p.kchunk * KB, kn = p.epi == EPI_WPART ? min(p.K - kb, p.kchunk * KB) : p.K;
+      const float g = bias_sum<T, BM, NT>(p, m0, kb, kn, (float*)smem);
+      const int m = m0 + (int)threadIdx.x;
+      if ((int)threadIdx.x < BM && m < p.M) {
+        if (p.epi == EPI_WPART) {
+          G((float*)((char*)p.ws + wsoff))[((int64_t)split * p.M + m) * p.ldws + p.nsplit] = g;
+        } else {
+          const int mdl = p.row_model ? p.row_model[m] : p.model;
+          if (keep_grads) p.dbias[m] = g;
+          if constexpr (OPT) p.bmaster[m] = opt_update1(opt[mdl], g, p.bmaster[m], p.sb1 + m, p.sb2 + m);
+          else p.bmaster[m] = fmaf(-(lrv ? lrv[mdl] : lr), g, p.bmaster[m]);
+        }
+      }
+      return;
+    }
+  }
   constexpr int PAD = sizeof(T) == 2 ? KMAJ_PAD_BF16 : KMAJ_PAD_F32;
   // the k range of this tile: all of K, or the split's chunk of kchunk k-blocks
   // (of KB columns, whatever the variant's own) from k0 on
@@ -1554,7 +1631,7 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
     // the launch's reused operands from L2.
     KRowLoader<T, BM, BK, NT, D, PAD> la;
     KRowLoader<T, BN, BK, NT, D, PAD> lb;
-    const int bcol = p.nsplit - n0;
+    const int bcol = p.bias_tile ? -1 : p.nsplit - n0;
     la.init((const T*)p.A + k0 * p.lda, p.lda, m0, kc, -1);
     lb.init((const T*)p.B + k0 * p.ldb, p.ldb, n0, kc, bcol >= 0 && bcol < BN ? bcol : -1);
     gemm_loop<T, BM, BN, BK, D, MM, OP_KMAJ, OP_KMAJ>(la, lb, nkb, (T*)smem, acc, [&] {

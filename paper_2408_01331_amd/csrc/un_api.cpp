@@ -754,7 +754,7 @@ static void build_tables(un_ctx* c, Tables& T) {
       bool wide = false;
       const GemmTile tl = gemm_tile(bf, GEMM_LARGE);
       for (const GemmProb& p : ps) {
-        large += (int64_t)cdiv(p.M, tl.bm) * cdiv(p.N, tl.bn) * (p.epi == EPI_WPART ? p.splits : 1);
+        large += (int64_t)cdiv(p.M, tl.bm) * (cdiv(p.N, tl.bn) + p.bias_tile) * (p.epi == EPI_WPART ? p.splits : 1);
         wide = wide || (p.ce_part && p.N > gemm_tile(bf, GEMM_SMALL).bn);
       }
       if (large <= GEMM_SMALL_MAX) variant = wide ? GEMM_WIDE : GEMM_SMALL;
@@ -776,7 +776,7 @@ static void build_tables(un_ctx* c, Tables& T) {
     int runs = 0;
     for (size_t k = 0; k < ps.size(); ++k) {
       GemmProb& p = ps[k];
-      const int tm = cdiv(p.M, GBM), tn = cdiv(p.N, GBN);
+      const int tm = cdiv(p.M, GBM), tn = cdiv(p.N, GBN) + p.bias_tile;
       p.tiles_n = tn;
       // a split-K problem's splits are tile sets of their own (entry
       // split * tiles + tile); runs stay within one split
@@ -1131,6 +1131,15 @@ static void build_tables(un_ctx* c, Tables& T) {
   // writes the same weights. Conv blocks keep their own per-level launches
   // (data gradient, then split-K weight gradient); the split-K reductions
   // with their updates run in one launch after the last level.
+  // columns of a weight-gradient product over K inputs: the weights and the
+  // bias column, or the weights alone where they fill whole small tiles (by
+  // the block's shape, not the launch's variant: the two sum the bias gradient
+  // in different orders)
+  auto wgrad_cols = [&](GemmProb& p, int K) {
+    p.nsplit = K;
+    p.bias_tile = K % gemm_tile(bf, GEMM_SMALL).bn == 0 ? 1 : 0;
+    p.N = p.bias_tile ? K : K + 1;
+  };
   auto add_wgrad = [&](const Block& b, std::vector<GemmProb>& gp, std::vector<char>& cat_done,
                        std::vector<ReduceProb>& rp) {
     const int gi = c->models[b.model].group;
@@ -1150,10 +1159,9 @@ static void build_tables(un_ctx* c, Tables& T) {
         p.ldb = g.ldxin;
         p.bmode = OP_KMAJ;
         p.M = (int)run.second;
-        p.N = (int)g.in_feat + 1;
+        wgrad_cols(p, (int)g.in_feat);
         p.K = B;
         p.epi = EPI_WGRAD;
-        p.nsplit = (int)g.in_feat;
         p.C = ptr(sub(g.catgW, run.first * kin_p * 4));
         p.ldc = kin_p;
         p.dbias = (float*)ptr(sub(g.catgb, run.first * 4));
@@ -1177,10 +1185,9 @@ static void build_tables(un_ctx* c, Tables& T) {
     p.ldb = b.ldx;
     p.bmode = OP_KMAJ;
     p.M = b.N;
-    p.N = b.K + 1;
+    wgrad_cols(p, b.K);
     p.K = B * b.tokens;
     p.epi = EPI_WGRAD;
-    p.nsplit = b.K;
     p.C = ptr(b.gW);
     p.ldc = b.ldw;
     p.dbias = (float*)ptr(b.gb);
