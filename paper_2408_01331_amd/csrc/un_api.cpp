@@ -21,6 +21,8 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <tuple>
+#include <utility>
 #include <vector>
 
 #include "internal.h"
@@ -85,7 +87,7 @@ struct Block {
   int64_t ldy = 0;
   size_t G = NONE;         // gradient at this block's output, row-major
   int64_t ldg = 0;
-  size_t ws = NONE, ws_size = 0;
+  size_t ws = NONE, ws_size = 0, ws_limit_size = 0;
   int64_t ldws = 0;
   int splits = 1, kchunk = 0;
   // split-K of a long logits product (forward): its partials, summed by the
@@ -173,6 +175,7 @@ struct un_ctx {
   // (conv split-K partials, loss partials), one contiguous arena range;
   // wsoff relocates them (un_step_scratch), 0 otherwise
   size_t ws_lo = 0, ws_bytes = 0;
+  size_t ws_limit_bytes = 0;  // the size that un_step_scratch accepts a context by
   int64_t wsoff = 0;
   // a captured step (un_graph_capture)
   hipGraph_t graph = nullptr;
@@ -1593,18 +1596,29 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
           b.ldg = rup(b.N, 8);
           b.G = A.take((size_t)R * b.ldg * es);
           // split-K weight gradient for a long contraction (rows = samples x
-          // tokens): chunks of at most 16 k-blocks, partials in the workspace,
-          // summed in split order by the level's reduction launch, which
-          // applies the update. Depends only on this block's shape.
-          const int BKg = bf ? GEMM_BK_BF16 : GEMM_BK_F32, KCH = bf ? 16 : 32;
+          // tokens): chunks of k-blocks, partials in the workspace, summed in
+          // split order by the step's reduction launch, which applies the
+          // update. Depends only on this block's shape. A block of many tiles
+          // takes chunks of at most 16 (fp32: 32) k-blocks, since every split
+          // writes and reads its partials; one of at most 64 small tiles leaves
+          // CUs idle and takes chunks of 8 (attn8 368 -> 353 us per step, 362
+          // with 4; 5 fp32 attention models 146 -> 118 us).
+          const int BKg = bf ? GEMM_BK_BF16 : GEMM_BK_F32, u = gemm_tile(bf, GEMM_SMALL).bm;
+          const int KCH = bf ? 16 : 32, KCH_FEW = 8;
           const int nkb = cdiv(R, BKg);
-          if (nkb > KCH) {
-            b.splits = cdiv(nkb, KCH);
-            b.kchunk = cdiv(nkb, b.splits);
-            b.splits = cdiv(nkb, b.kchunk);
-            b.ldws = rup(b.K + 1, 4);
-            b.ws_size = (size_t)b.splits * b.N * b.ldws * 4;  // placed in the workspace range below
+          b.ldws = rup(b.K + 1, 4);
+          auto cut = [&](int chunk) {  // splits and chunk of nkb k-blocks in chunks of at most `chunk`
+            const int kc = cdiv(nkb, cdiv(nkb, chunk));
+            return std::make_pair(cdiv(nkb, kc), kc);
+          };
+          auto part_bytes = [&](int splits) { return (size_t)splits * b.N * b.ldws * 4; };
+          const int chunk = cdiv(b.N, u) * cdiv(b.K, u) <= 64 ? KCH_FEW : KCH;
+          if (nkb > chunk) {
+            std::tie(b.splits, b.kchunk) = cut(chunk);
+            b.ws_size = part_bytes(b.splits);  // placed in the workspace range below
           }
+          // its share of the size that un_step_scratch's limit is stated on
+          b.ws_limit_size = nkb > KCH ? part_bytes(cut(KCH).first) : 0;
         }
       } else {
         const int J = b.KH * b.KH * b.C;
@@ -1646,6 +1660,7 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
         b.splits = cdiv(nkb, b.kchunk);
         b.ldws = rup(J + 1, 4);
         b.ws_size = (size_t)b.splits * b.O * b.ldws * 4;  // placed in the workspace range below
+        b.ws_limit_size = b.ws_size;
       }
     }
     // wire inputs
@@ -1669,13 +1684,17 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
   c->ws_lo = (size_t)rup((int64_t)A.top, 256);
   A.top = c->ws_lo;
   c->ce_partial = A.take(c->models.size() * (size_t)cdiv(c->maxB, CE_ROWS) * 4);
+  Arena lim;  // the same range with the Linear weight gradients in chunks of 16 (fp32: 32) k-blocks
+  lim.top = A.top;
   for (auto& m : c->models)
-    for (auto& b : m.blocks)
-      {
-        if (b.ws_size) b.ws = A.take(b.ws_size);
-        if (b.fws_size) b.fws = A.take(b.fws_size);
-      }
+    for (auto& b : m.blocks) {
+      if (b.ws_size) b.ws = A.take(b.ws_size);
+      if (b.fws_size) b.fws = A.take(b.fws_size);
+      if (b.ws_limit_size) lim.take(b.ws_limit_size);
+      if (b.fws_size) lim.take(b.fws_size);
+    }
   c->ws_bytes = A.top - c->ws_lo;
+  c->ws_limit_bytes = lim.top - c->ws_lo;
 
   c->active.assign(c->models.size(), 1);
   Tables T;
@@ -2407,10 +2426,13 @@ un_status un_step_scratch(un_ctx* c, float lr, float* losses) {
   CHECK_CTX(c);
   if (!c->all_loaded()) return fail(c, UN_ERR_STATE, "un_step_scratch before a batch of every input group is loaded");
   if (!std::isfinite(lr)) return fail(c, UN_ERR_INVALID, "lr is not finite");
-  if (c->ws_bytes > UN_SCRATCH_BYTES)
-    return fail(c, UN_ERR_UNSUPPORTED, "this context's step workspace (" + std::to_string(c->ws_bytes) +
+  if (c->ws_limit_bytes > UN_SCRATCH_BYTES)
+    return fail(c, UN_ERR_UNSUPPORTED, "this context's step workspace (" + std::to_string(c->ws_limit_bytes) +
                                            " bytes) exceeds the library's static scratch (" +
                                            std::to_string(UN_SCRATCH_BYTES) + " bytes); use un_step");
+  // an accepted context whose finer weight-gradient chunks outgrow the array
+  // runs in its own workspace, which un_create allocated
+  if (c->ws_bytes > UN_SCRATCH_BYTES) return step_common(c, lr, nullptr, losses);
   char* ptr = nullptr;
   un_status st = scratch_on(c, &ptr);
   if (st != UN_OK) return st;

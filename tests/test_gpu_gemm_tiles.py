@@ -53,3 +53,24 @@ def test_alone_equals_in_a_large_launch(precision, batch, classes, widths):
     x, y = W.make_batch(wl([spec]), 0)
     lo, _, _ = oracle.step(spec, W.init_params(spec, (104,), 9, 0), x, y, 0.05, precision)
     assert abs(alone[0][0, 0] - lo) <= 1e-5 * abs(lo)
+
+
+def test_scratch_step_beyond_the_array():
+    """40 fp32 MLPs at batch 1024: within the scratch step's limit, which counts
+    chunks of 1024 rows (none here), but their chunks of 256 rows need 40 MiB of
+    partials. The step runs, in the arena, and equals un_step bit for bit."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2408_01331_amd import unifiednn as U
+    n = 40
+    wl = W.Workload("t", n, 1024, (64,), "f32", [_mlp([256, 256], 10)] * n, 0.05, 1, 9)
+    x, y = W.make_batch(wl, 0)
+    out = []
+    for step in (U.un_step, U.un_step_scratch):
+        with U.Hybrid(wl.specs, wl.batch, wl.in_shape, "f32", seeds=list(range(n))) as h:
+            h.load_batch(x, y)
+            losses = step(h.ctx, 0.05, n)
+            out.append((losses, h.get_params(0), h.get_params(n - 1)))
+    for a, b in zip(*out):
+        assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
