@@ -317,8 +317,9 @@ un_status un_set_opt_state(un_ctx* ctx, int32_t i, const float* src, size_t n_el
  * two contexts on two streams at once - race; serialise them.
  * Errors: as un_step, and UN_ERR_UNSUPPORTED (nothing runs) when this
  * context's workspace exceeds the array (wide CNN hybrids; use un_step),
- * counted with Linear weight gradients in chunks of 1024 rows; a context within
- * that limit whose finer chunks need more runs in its arena's workspace. */
+ * counted with the models' own channel counts and with Linear weight gradients
+ * in chunks of 1024 rows; a context within that limit whose padded channels or
+ * finer chunks need more runs in its arena's workspace. */
 un_status un_step_scratch(un_ctx* ctx, float lr, float* losses);
 
 /* Number of parameters of model i. */

@@ -67,10 +67,13 @@ struct Block {
   int res_from = -1, res_to = -1;
   // linear
   int K = 0, N = 0;
+  int Kr = 0;  // the model's own inputs; K (stored) is larger behind a conv with padded channels
   int in_c = 0, in_h = 1, in_w = 1;  // input viewed as an image (Flatten order mapping)
   // conv
   int C = 0, H = 0, W = 0, O = 0, KH = 0, pad = 0, OH = 0, OW = 0, PH = 0, PW = 0;
-  int Cr = 0;  // the model's input channels; C (stored channels) is larger for a padded network input
+  // the model's own channels; the stored ones, C and O, are larger where they
+  // are padded to whole 16-byte vectors (pad_channels, a padded network input)
+  int Cr = 0, Or = 0;
   // PyTorch-layout offsets in the model's flat parameter vector
   size_t pt_w = 0, pt_b = 0, n_w = 0, n_b = 0;
   // arena offsets (NONE = absent)
@@ -247,6 +250,44 @@ un_status fail(un_ctx* c, un_status s, const std::string& msg) {
 // --------------------------------------------------------------------------
 // Spec parsing
 // --------------------------------------------------------------------------
+// The conv kernels address each activation, gradient and weight tensor with
+// 32-bit offsets (buffer loads take byte offsets below 2^31), and an output row
+// of elements with 24-bit multiplies: can they, with C input and O output
+// channels stored?
+bool conv_addressable(const Block& b, int64_t C, int64_t O, int64_t batch, int64_t es) {
+  const int64_t lim = (int64_t)1 << 31, row = (int64_t)1 << 24;
+  const int64_t biggest = std::max({batch * C * b.H * b.W, batch * O * b.OH * b.OW, O * (b.KH * b.KH * C + 8)});
+  return biggest * es < lim && b.OW * O < row && b.W * C < row;
+}
+
+// Store a CNN's channels padded to whole 16-byte vectors: the vector loaders
+// and halo tiles then serve every channel count. A padded channel has zero
+// weights and bias, so its activation and gradient are zero, so every gradient
+// that involves it is exactly zero and under each optimizer it stays zero. A
+// model whose padded tensors would outgrow the kernels' offsets keeps its own
+// channel counts and the element-wise loaders.
+void pad_channels(Model& m, int batch, int vec, int es) {
+  for (auto& b : m.blocks) b.Kr = b.K;
+  auto padded = [&](int o) { return (int)rup(o, vec); };
+  int prev = 0;
+  for (auto& b : m.blocks) {
+    if (b.kind != 1) break;
+    if (!conv_addressable(b, prev ? prev : b.C, padded(b.O), batch, es)) return;
+    prev = padded(b.O);
+  }
+  for (size_t j = 0; j < m.blocks.size(); ++j) {
+    Block& b = m.blocks[j];
+    const bool after_conv = j > 0 && m.blocks[j - 1].kind == 1;
+    if (b.kind == 1) {
+      if (after_conv) b.C = m.blocks[j - 1].O;
+      b.O = padded(b.O);
+    } else if (b.kind == 0 && after_conv) {
+      b.in_c = m.blocks[j - 1].O;
+      b.K = b.in_c * b.in_h * b.in_w;
+    }
+  }
+}
+
 un_status parse_model(const un_model_spec& s, const un_input_spec& in, int mi, Model& m, std::string& why) {
   if (s.n_layers <= 0 || !s.layers) {
     why = "model " + std::to_string(mi) + ": no layers";
@@ -348,7 +389,7 @@ un_status parse_model(const un_model_spec& s, const un_input_spec& in, int mi, M
       b.Cr = c;
       b.H = h;
       b.W = w;
-      b.O = L.out;
+      b.O = b.Or = L.out;
       b.KH = L.kernel;
       b.pad = L.pad;
       b.OH = h + 2 * L.pad - L.kernel + 1;
@@ -357,17 +398,9 @@ un_status parse_model(const un_model_spec& s, const un_input_spec& in, int mi, M
         why = where(i) + "kernel larger than padded input";
         return UN_ERR_INVALID;
       }
-      {
-        // the conv kernels address each activation, gradient and weight tensor
-        // with 32-bit offsets (buffer loads take byte offsets below 2^31), and
-        // an output row of elements with 24-bit multiplies
-        const int64_t es = in.precision == UN_BF16_F32MASTER ? 2 : 4, lim = (int64_t)1 << 31;
-        const int64_t biggest = std::max({(int64_t)in.batch * c * h * w, (int64_t)in.batch * b.O * b.OH * b.OW,
-                                          (int64_t)b.O * (L.kernel * L.kernel * c + 8)});
-        if (biggest * es >= lim || (int64_t)b.OW * b.O >= ((int64_t)1 << 24) || (int64_t)w * c >= ((int64_t)1 << 24)) {
-          why = where(i) + "conv tensors of 2^31 bytes or more, or output rows of 2^24 elements or more, are not supported";
-          return UN_ERR_UNSUPPORTED;
-        }
+      if (!conv_addressable(b, b.C, b.O, in.batch, in.precision == UN_BF16_F32MASTER ? 2 : 4)) {
+        why = where(i) + "conv tensors of 2^31 bytes or more, or output rows of 2^24 elements or more, are not supported";
+        return UN_ERR_UNSUPPORTED;
       }
       b.n_w = (size_t)b.O * c * L.kernel * L.kernel;
       b.n_b = b.O;
@@ -1532,6 +1565,8 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
     }
   }
 
+  for (auto& m : c->models) pad_channels(m, c->groups[m.group].B, vec, (int)es);
+
   // --- per block buffers
   int levels = 0;
   for (size_t mi = 0; mi < c->models.size(); ++mi) {
@@ -1644,7 +1679,6 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
         const int BMc = bf ? CONV_BM_BF16 : CONV_BM_F32, BNc = bf ? CONV_BN_BF16 : CONV_BN_F32;
         const int64_t kpix = b.pool ? (int64_t)B * b.PH * b.PW * 4 : (int64_t)B * b.OH * b.OW;
         const int nkb = cdiv(kpix, BK);
-        const int tiles = cdiv(b.O, BMc) * cdiv(J + 1, BNc);
         // >= 4 k-blocks per split and at most 64 workgroups: 64 is the
         // concurrent capacity of one XCD (32 CUs x 2), so the problems of a
         // launch fill whole rounds instead of leaving a short extra one.
@@ -1652,15 +1686,21 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
         // element-wise loaders (several times slower per k-block): chunks of
         // 8 k-blocks, up to 512 workgroups. fp32 blocks with small partials
         // (<= 64 KiB per split): chunks of 16 k-blocks, up to 256 workgroups.
-        int splits = std::max(1, std::min(nkb / 4, 64 / tiles));
-        const int vec = bf ? 8 : 4;
-        if (b.O % vec != 0 || b.C % vec != 0) splits = std::max(splits, std::min(nkb / 8, 512 / tiles));
-        else if (!bf && (int64_t)b.O * rup(J + 1, 4) * 4 <= 65536) splits = std::max(splits, std::min(nkb / 16, 256 / tiles));
-        b.kchunk = cdiv(nkb, splits);
-        b.splits = cdiv(nkb, b.kchunk);
+        auto cut = [&](int O, int C, int& kchunk) {  // splits of a block of O x (KH KH C + 1)
+          const int Jc = b.KH * b.KH * C, tiles = cdiv(O, BMc) * cdiv(Jc + 1, BNc);
+          int n = std::max(1, std::min(nkb / 4, 64 / tiles));
+          if (O % vec != 0 || C % vec != 0) n = std::max(n, std::min(nkb / 8, 512 / tiles));
+          else if (!bf && (int64_t)O * rup(Jc + 1, 4) * 4 <= 65536) n = std::max(n, std::min(nkb / 16, 256 / tiles));
+          kchunk = cdiv(nkb, n);
+          return cdiv(nkb, kchunk);
+        };
+        b.splits = cut(b.O, b.C, b.kchunk);
         b.ldws = rup(J + 1, 4);
         b.ws_size = (size_t)b.splits * b.O * b.ldws * 4;  // placed in the workspace range below
-        b.ws_limit_size = b.ws_size;
+        // un_step_scratch's limit counts the model's own channels
+        int kc;
+        const int C0 = j == 0 ? b.C : b.Cr;
+        b.ws_limit_size = (size_t)cut(b.Or, C0, kc) * b.Or * rup(b.KH * b.KH * C0 + 1, 4) * 4;
       }
     }
     // wire inputs
@@ -1684,7 +1724,9 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
   c->ws_lo = (size_t)rup((int64_t)A.top, 256);
   A.top = c->ws_lo;
   c->ce_partial = A.take(c->models.size() * (size_t)cdiv(c->maxB, CE_ROWS) * 4);
-  Arena lim;  // the same range with the Linear weight gradients in chunks of 16 (fp32: 32) k-blocks
+  // the same range with unpadded channels and the Linear weight gradients in
+  // chunks of 16 (fp32: 32) k-blocks: what un_step_scratch's limit is stated on
+  Arena lim;
   lim.top = A.top;
   for (auto& m : c->models)
     for (auto& b : m.blocks) {
@@ -1758,33 +1800,34 @@ static void to_internal(const Block& b, const float* pt, std::vector<float>& w, 
   if (b.kind == 0) {
     w.assign((size_t)b.N * b.ldw, 0.f);
     for (int o = 0; o < b.N; ++o)
-      for (int k = 0; k < b.K; ++k) w[(size_t)o * b.ldw + lin_col(b, k)] = pt[b.pt_w + (size_t)o * b.K + k];
+      for (int k = 0; k < b.Kr; ++k) w[(size_t)o * b.ldw + lin_col(b, k)] = pt[b.pt_w + (size_t)o * b.Kr + k];
     bias.assign(pt + b.pt_b, pt + b.pt_b + b.N);
   } else {
     w.assign((size_t)b.O * b.ldw, 0.f);
-    for (int o = 0; o < b.O; ++o)
+    for (int o = 0; o < b.Or; ++o)
       for (int ci = 0; ci < b.Cr; ++ci)
         for (int u = 0; u < b.KH; ++u)
           for (int v = 0; v < b.KH; ++v)
             w[(size_t)o * b.ldw + ((size_t)u * b.KH + v) * b.C + ci] =
                 pt[b.pt_w + (((size_t)o * b.Cr + ci) * b.KH + u) * b.KH + v];
-    bias.assign(pt + b.pt_b, pt + b.pt_b + b.O);
+    bias.assign(b.O, 0.f);
+    std::copy(pt + b.pt_b, pt + b.pt_b + b.Or, bias.begin());
   }
 }
 
 static void from_internal(const Block& b, const std::vector<float>& w, const std::vector<float>& bias, float* pt) {
   if (b.kind == 0) {
     for (int o = 0; o < b.N; ++o)
-      for (int k = 0; k < b.K; ++k) pt[b.pt_w + (size_t)o * b.K + k] = w[(size_t)o * b.ldw + lin_col(b, k)];
+      for (int k = 0; k < b.Kr; ++k) pt[b.pt_w + (size_t)o * b.Kr + k] = w[(size_t)o * b.ldw + lin_col(b, k)];
     std::copy(bias.begin(), bias.end(), pt + b.pt_b);
   } else {
-    for (int o = 0; o < b.O; ++o)
+    for (int o = 0; o < b.Or; ++o)
       for (int ci = 0; ci < b.Cr; ++ci)
         for (int u = 0; u < b.KH; ++u)
           for (int v = 0; v < b.KH; ++v)
             pt[b.pt_w + (((size_t)o * b.Cr + ci) * b.KH + u) * b.KH + v] =
                 w[(size_t)o * b.ldw + ((size_t)u * b.KH + v) * b.C + ci];
-    std::copy(bias.begin(), bias.end(), pt + b.pt_b);
+    std::copy(bias.begin(), bias.begin() + b.Or, pt + b.pt_b);
   }
 }
 
@@ -1845,7 +1888,7 @@ static void init_host(const Model& m, std::vector<float>& pt) {
   int t = 0;
   for (auto& b : m.blocks) {
     if (b.kind == 2) continue;
-    const double fan_in = b.kind == 0 ? (double)b.K : (double)b.Cr * b.KH * b.KH;
+    const double fan_in = b.kind == 0 ? (double)b.Kr : (double)b.Cr * b.KH * b.KH;
     const double wb = std::sqrt(6.0 / fan_in), bb = 1.0 / std::sqrt(fan_in);
     for (int part = 0; part < 2; ++part, ++t) {
       const size_t off = part == 0 ? b.pt_w : b.pt_b, n = part == 0 ? b.n_w : b.n_b;

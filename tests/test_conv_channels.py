@@ -1,0 +1,89 @@
+"""Channel counts that are no whole 16-byte vectors: stored padded with zero
+channels, which must never show - in parameters, gradients, optimizer state,
+losses - and never become non-zero."""
+import numpy as np
+import pytest
+
+from paper_2408_01331_amd import workloads as W
+from _parity import compare_run, compare_step, run_gpu, run_oracle
+
+L, C, R, POOL, FLAT, RB, RE = (lambda n: ("linear", n)), (lambda *a: ("conv",) + a), ("relu",), ("pool",), \
+    ("flatten",), ("res_begin",), ("res_end",)
+
+
+def _specs():
+    return [
+        # one channel, then three, unpooled and without a ReLU, odd maps
+        {"layers": [C(1, 3, 1), R, POOL, C(3, 3, 0), C(8, 3, 1), R, FLAT, L(10)], "num_classes": 10},
+        # a residual block of padded channels
+        {"layers": [C(6, 3, 1), R, POOL, RB, C(6, 3, 1), R, C(6, 3, 1), RE, R, C(7, 3, 1), R, POOL, C(8, 1, 0), R, FLAT,
+                    L(10)], "num_classes": 10},
+        # LeNet-like: 5x5 without padding
+        {"layers": [C(9, 5, 0), R, POOL, C(16, 5, 0), R, POOL, FLAT, L(20), R, L(10)], "num_classes": 10},
+    ]
+
+
+def _wl(precision, specs=None, steps=2):
+    specs = _specs() if specs is None else specs
+    return W.Workload("channels", len(specs), 13, (3, 28, 28), precision, specs, 0.02, steps, 4, init="torch")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["f32", "bf16"])
+def test_against_the_oracle_and_alone(precision):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = _wl(precision)
+    m = list(range(wl.n_models))
+    orc, spread = run_oracle(wl, 1, m, spread=True)
+    print(compare_step(wl, run_gpu(wl, 1), orc, m, spread=spread))
+    merged = run_gpu(wl, 2)
+    orc, spread = run_oracle(wl, 2, m, spread=True)
+    print(compare_run(wl, merged, orc, m, spread=spread))
+    for i in m:
+        solo = run_gpu(_wl(precision, [wl.specs[i]]), 2, theta={0: W.init_params(wl.specs[i], wl.in_shape, 4, i, "torch")})
+        for a, b in zip([merged[0][:, i]] + merged[1][i] + merged[2][i], [solo[0][:, 0]] + solo[1][0] + solo[2][0]):
+            assert np.array_equal(np.asarray(a, np.float32).view(np.uint32), np.asarray(b, np.float32).view(np.uint32))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["momentum", "adam"])
+def test_parameters_and_state_round_trip(kind):
+    """What set_params / set_opt_state put in, get_* gives back, and a run
+    continued in a fresh context equals the run it left."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2408_01331_amd.unifiednn import Hybrid
+    wl = _wl("f32")
+
+    def fresh():
+        h = Hybrid(wl.specs, wl.batch, wl.in_shape, "f32", seeds=[7, 8, 9])
+        for i in range(h.n):
+            h.set_optimizer(i, kind, momentum=0.9)
+        h.load_batch(*W.make_batch(wl, 0))
+        return h
+
+    with fresh() as a, fresh() as b:
+        a.step(1e-3)
+        for i in range(a.n):
+            b.set_params(i, a.get_params(i))
+            b.set_opt_state(i, *a.get_opt_state(i))
+            assert np.array_equal(a.get_params(i), b.get_params(i))
+            assert np.array_equal(a.get_opt_state(i)[0], b.get_opt_state(i)[0])
+        la, lb = a.step(1e-3), b.step(1e-3)
+        assert np.array_equal(la, lb)
+        for i in range(a.n):
+            assert np.array_equal(a.get_params(i), b.get_params(i))
+
+
+def test_planner_takes_channels_it_cannot_pad():
+    """One-channel bf16 maps of 128 x 1024 x 1024 pass 2^31 bytes only when padded
+    to 8 channels: the model is accepted and keeps its one channel, while at
+    batch 64 it is padded."""
+    from paper_2408_01331_amd.unifiednn import un_plan_bytes
+    spec = {"layers": [C(1, 1, 256), POOL, C(8, 1, 0), POOL, FLAT, L(10)], "num_classes": 10}
+    half, full = (un_plan_bytes([spec], b, (8, 512, 512), "bf16")[0] for b in (64, 128))
+    # activation and gradient of the pooled one-channel map: 8 channels at batch 64, one at 128
+    assert full < 2 * half - 2 * 64 * 512 * 512 * 2 * 6
