@@ -106,8 +106,9 @@ struct GemmProb {
 //
 // Halo tiling (fwd and dgrad, when the row-tile geometry fits, halo != 0): a
 // tile of BM rows is `imgs` whole images or `tr` whole rows of one image of
-// the pass's pixel space (fwd: conv output OHxOW; dgrad: conv input HxW). The
-// workgroup stages the operand rows that tile reads - `hr` rows x `hc`
+// the pass's pixel space (fwd: conv output OHxOW, pooled the 2PHx2PW that the
+// windows cover; dgrad: conv input HxW), `rows` <= BM of them (the rest of the
+// tile is not stored; an image's last tile may hold fewer rows). The workgroup stages the operand rows that tile reads - `hr` rows x `hc`
 // columns per image, channels in blocks of `cb` (LDS stride `cs`) - once per
 // channel block in LDS, and reads every kernel tap from there; k runs over
 // (channel block, tap, channel in block). Weight columns keep the (tap, c)
@@ -119,6 +120,7 @@ struct ConvProb {
   int32_t M, N, K;            // GEMM sizes of this pass
   int32_t tiles_m, tiles_n, splits, kchunk;
   int32_t halo, tr, imgs, hr, hc, cb, cs;  // halo tiling (see above)
+  int32_t rows, tpi;                       // rows of a full tile; row tiles per image
   int32_t bm, bn;                          // halo tile shape
   // forward halo passes with one channel block: consecutive m-tiles of one
   // n-column per workgroup (weights and tap tables loaded once, the next
@@ -345,8 +347,10 @@ constexpr int REDUCE_BLOCK = 256;
 constexpr int CE_MAX_BATCH = 1 << 20;
 constexpr int CE_ROWS = 32;           // sample rows per softmax-CE block
 constexpr int CE_LANES = 8;           // lanes per row
-// Halo tiles. Two shapes: wide BM x BN = CONV_BM x CONV_BN, and narrow
-// (2*CONV_BM) x (CONV_BN/2) for passes with at most CONV_BN/2 output columns.
+// Halo tiles. Shapes: wide BM x BN = CONV_BM x CONV_BN, narrow (2*CONV_BM) x
+// (CONV_BN/2) for passes with at most CONV_BN/2 output columns, and, of the
+// same width, tall 4*CONV_BM (large bf16 forward passes), and slim (4*CONV_BM) x
+// (CONV_BN/4) (fp32 passes of at most CONV_BN/4 columns).
 // LDS per workgroup: the double-buffered weight stage, two chunk tables of
 // HALO_QMAX ints, and the staged rows - halo_elems() elements.
 constexpr int HALO_QMAX = 256;

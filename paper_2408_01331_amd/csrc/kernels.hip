@@ -140,12 +140,12 @@ __device__ __forceinline__ u32x4 zero4() { return u32x4{0u, 0u, 0u, 0u}; }
 // ---------------------------------------------------------------------------
 // MFMA core
 // ---------------------------------------------------------------------------
-// NW waves per workgroup: 4 as 2 x 2 (m x n), 8 as 2 x 4, 16 as 4 x 4.
+// NW waves per workgroup: 4 as 2 x 2 (m x n; 4 x 1 for 16 columns), 8 as 2 x 4, 16 as 4 x 4.
 template <typename T, int BM, int BN, int BK, int NW = 4>
 struct Tile {
   static constexpr int VEC = TT<T>::VEC;
   static constexpr int LDK = BK + UN_LDS_PAD_CHUNKS * VEC;  // LDS row stride in elements (16-byte pad chunks)
-  static constexpr int WGN = NW == 4 ? 2 : 4, WGM = NW / WGN, NT = 64 * NW;
+  static constexpr int WGN = NW == 4 ? (BN == 16 ? 1 : 2) : 4, WGM = NW / WGN, NT = 64 * NW;
   static constexpr int WM = BM / WGM, WN = BN / WGN;
   static constexpr int FM = WM / 16, FN = WN / 16;
   static_assert(NW == 4 || NW == 8 || NW == 16, "4, 8 or 16 waves");
@@ -1912,7 +1912,8 @@ struct Acc32 {
 // Conv forward epilogue: ReLU, 2x2 max-pool in registers (pool rows are
 // window-ordered, so a lane's four accumulator rows are one window), then the
 // pooled value and its one-hot argmax, stored straight from registers
-// (staging this small output in LDS measured slower). One straight-line
+// (staging this small output in LDS measured slower). The tile's rows are
+// output rows m0 .. M - 1 (the rest of it is not stored). One straight-line
 // variant per (ReLU, pool, skip input) pattern, chosen by a uniform branch.
 //
 // Pooling takes the maximum of the raw sums, then adds the bias and applies
@@ -1960,11 +1961,11 @@ __device__ __forceinline__ void store_relu(__amdgpu_buffer_rsrc_t r, uint32_t vb
 }
 
 template <typename T, class L, bool RELU, bool POOL, bool RES>
-__device__ __forceinline__ void conv_fwd_epi(const ConvProb& p, int m0, int n0, const typename L::Acc& acc) {
+__device__ __forceinline__ void conv_fwd_epi(const ConvProb& p, int m0, int M, int n0, const typename L::Acc& acc) {
   // the problem's fields as values: read through the problem reference,
   // every field would be loaded again after each store (the stores might
   // alias it)
-  const int O = p.O, M = p.M;
+  const int O = p.O;
   // outputs through buffer stores: 32-bit offsets (tensors are under 2^31
   // bytes), no 64-bit address arithmetic per store
   const __amdgpu_buffer_rsrc_t rP = make_rsrc(p.P, 0x7fffffff), rAM = make_rsrc(p.amax, 0x7fffffff);
@@ -1987,16 +1988,14 @@ __device__ __forceinline__ void conv_fwd_epi(const ConvProb& p, int m0, int n0, 
       const int o = n0 + cl;
       float v[4] = {a[0], a[1], a[2], a[3]};
       if constexpr (POOL) {
-        // window (m0 + lrow + urow) / 4; 24-bit multiplies (pixel and
-        // channel counts are under 2^24)
-        const uint32_t e = (uint32_t)(__mul24((m0 + lrow) >> 2, O) + o);
+        const uint32_t e = (uint32_t)(((m0 + lrow) >> 2) * O + o);
         const int se = (urow >> 2) * O;
         uint32_t am;
         const float mx = pool4<RELU>(v, bias[j], am);
         store_relu<T, RELU>(rP, o < O ? e * (uint32_t)sizeof(T) : OUT, se * (int)sizeof(T), mx);
         __builtin_amdgcn_raw_buffer_store_b8((uint8_t)am, rAM, o < O ? e : OUT, se, 0);
       } else {
-        const uint32_t e = (uint32_t)(__mul24(m0 + lrow, O) + o), vb = o < O ? e * (uint32_t)sizeof(T) : OUT;
+        const uint32_t e = (uint32_t)((m0 + lrow) * O + o), vb = o < O ? e * (uint32_t)sizeof(T) : OUT;
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] += bias[j];
         if constexpr (sizeof(T) == 2) {
@@ -2028,14 +2027,14 @@ __device__ __forceinline__ void conv_fwd_epi(const ConvProb& p, int m0, int n0, 
     for (int r = 0; r < 4; ++r) {
       v[r] = POOL ? a[r] : a[r] + bias[j];
       // skip input of a residual block (never pooled): rows are pixels
-      if constexpr (RES) v[r] += mb + r < M ? TT<T>::to_f(R[__mul24(mb + r, O) + o]) : 0.f;
+      if constexpr (RES) v[r] += mb + r < M ? TT<T>::to_f(R[(mb + r) * O + o]) : 0.f;
       if constexpr (RELU && !POOL) v[r] = fmaxf(v[r], 0.f);
     }
     if constexpr (POOL) {
       // rows mb..mb+3 are one 2x2 window
       uint32_t am;
       const float mx = pool4<RELU>(v, bias[j], am);
-      const int e = __mul24(mb >> 2, O) + o;
+      const int e = (mb >> 2) * O + o;
       store_relu<T, RELU>(rP, (uint32_t)e * (uint32_t)sizeof(T), 0, mx);
       __builtin_amdgcn_raw_buffer_store_b8((uint8_t)am, rAM, e, 0, 0);
     } else {
@@ -2043,35 +2042,35 @@ __device__ __forceinline__ void conv_fwd_epi(const ConvProb& p, int m0, int n0, 
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         if (r >= nv) break;
-        buf_store_t<T>(rP, __mul24(mb + r, O) + o, v[r]);
+        buf_store_t<T>(rP, (mb + r) * O + o, v[r]);
       }
     }
   });
 }
 
 template <typename T, class L>
-__device__ __forceinline__ void conv_fwd_epilogue(const ConvProb& p, int m0, int n0, const typename L::Acc& acc) {
+__device__ __forceinline__ void conv_fwd_epilogue(const ConvProb& p, int m0, int M, int n0, const typename L::Acc& acc) {
   const bool relu = p.relu != 0;
   if (p.R) {  // residual blocks are never pooled
-    if (relu) conv_fwd_epi<T, L, true, false, true>(p, m0, n0, acc);
-    else conv_fwd_epi<T, L, false, false, true>(p, m0, n0, acc);
+    if (relu) conv_fwd_epi<T, L, true, false, true>(p, m0, M, n0, acc);
+    else conv_fwd_epi<T, L, false, false, true>(p, m0, M, n0, acc);
   } else if (p.pool) {
-    if (relu) conv_fwd_epi<T, L, true, true, false>(p, m0, n0, acc);
-    else conv_fwd_epi<T, L, false, true, false>(p, m0, n0, acc);
+    if (relu) conv_fwd_epi<T, L, true, true, false>(p, m0, M, n0, acc);
+    else conv_fwd_epi<T, L, false, true, false>(p, m0, M, n0, acc);
   } else {
-    if (relu) conv_fwd_epi<T, L, true, false, false>(p, m0, n0, acc);
-    else conv_fwd_epi<T, L, false, false, false>(p, m0, n0, acc);
+    if (relu) conv_fwd_epi<T, L, true, false, false>(p, m0, M, n0, acc);
+    else conv_fwd_epi<T, L, false, false, false>(p, m0, M, n0, acc);
   }
 }
 
 // Conv data-gradient epilogue: the previous block's ReLU' (its stored output
 // > 0) and the store of the gradient at that output, in 16-byte vectors.
 template <typename T, int BM, int BN, class L>
-__device__ __forceinline__ void conv_dgrad_epilogue(const ConvProb& p, int m0, int n0, const typename L::Acc& acc,
-                                                    char* smem) {
+__device__ __forceinline__ void conv_dgrad_epilogue(const ConvProb& p, int m0, int M, int n0,
+                                                    const typename L::Acc& acc, char* smem) {
   using ES = ConvEpiSmem<T, BM, BN>;
   constexpr int VE = ES::VE, CPR = BN / VE, NT = L::NT;
-  const int C = p.C, M = p.M;
+  const int C = p.C;
   const bool prev_relu = p.prev_relu != 0;
   const gptr<const T> R = G((const T*)p.R);
   const gptr<const T> X = G((const T*)p.X);
@@ -2148,7 +2147,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
   lb.init((const T*)p.Wt + (int64_t)n0 * p.ldw, p.ldw, p.N - n0, p.K);
   mma_loop<T, BM, BN, BK>(la, lb, 0, (p.K + BK - 1) / BK, (T*)smem, acc);
 
-  conv_fwd_epilogue<T, L>(p, m0, n0, acc);
+  conv_fwd_epilogue<T, L>(p, m0, p.M, n0, acc);
 }
 
 template <typename T, int BM, int BN, int BK>
@@ -2174,7 +2173,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
   lb.init((const T*)p.Wt + (int64_t)n0 * p.ldw, p.ldw, p.N - n0, p.K);
   mma_loop<T, BM, BN, BK>(la, lb, 0, (p.K + BK - 1) / BK, (T*)smem, acc);
 
-  conv_dgrad_epilogue<T, BM, BN, Acc16<T, BM, BN, BK, 4>>(p, m0, n0, acc, smem);
+  conv_dgrad_epilogue<T, BM, BN, Acc16<T, BM, BN, BK, 4>>(p, m0, p.M, n0, acc, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -2396,8 +2395,8 @@ __device__ __forceinline__ void put_halo(T* sH, const u32x4 (&v)[PF], const int 
 // offset of chunk 8 kb + 2 s + h (clamped to the last chunk), so a lane reads
 // the four it needs at once.
 template <int BM, int BN, int BK, int NW>
-__device__ __forceinline__ void mma_halo(const bf16_t* sH, const int (&hbase)[Acc32<BM, BN, NW>::FM], const int* qa,
-                                         int q0, int nq, const bf16_t* sB, typename Acc32<BM, BN, NW>::Acc& acc) {
+__device__ __forceinline__ void mma_halo_bf16(const bf16_t* sH, const int (&hbase)[Acc32<BM, BN, NW>::FM], const int* qa,
+                                              int q0, int nq, const bf16_t* sB, typename Acc32<BM, BN, NW>::Acc& acc) {
   using L = Acc32<BM, BN, NW>;
   constexpr int LDK = Tile<bf16_t, BM, BN, BK, NW>::LDK;
   static_assert(BK == 64, "eight chunks per k-block, four k-steps");
@@ -2423,7 +2422,7 @@ __device__ __forceinline__ void mma_halo(const bf16_t* sH, const int (&hbase)[Ac
 
 // fp32: 16x16x4 MFMA blocks (Acc16).
 template <int BM, int BN, int BK, int NW>
-__device__ __forceinline__ void mma_halo(const float* sH, const int (&hbase)[Acc16<float, BM, BN, BK, NW>::FM],
+__device__ __forceinline__ void mma_halo_f32(const float* sH, const int (&hbase)[Acc16<float, BM, BN, BK, NW>::FM],
                                          const int* qa, int q0, int nq, const float* sB,
                                          typename Acc16<float, BM, BN, BK, NW>::Acc& acc) {
   using TL = Tile<float, BM, BN, BK, NW>;
@@ -2480,34 +2479,31 @@ __device__ __forceinline__ void halo_tile(const ConvProb& p, int local, char* sm
   T* sH = (T*)(qb + HALO_QMAX);
   const int tm0 = local / p.tiles_n, tn = local - tm0 * p.tiles_n;
   const int n0 = tn * BN;
-  const int SH = DGRAD ? p.H : p.OH, SW = DGRAD ? p.W : p.OW;
+  // the pass's pixel space; a pooled forward pass covers whole windows only
+  const bool wo = !DGRAD && p.pool;  // window order: r = 4 * window + (dy, dx)
+  const int SH = DGRAD ? p.H : wo ? 2 * p.PH : p.OH, SW = DGRAD ? p.W : wo ? 2 * p.PW : p.OW;
   // (not the tall tiles: their accumulators leave no registers for the
   // fetched rows across the epilogue; the host plans none)
   constexpr bool MULTI = !DGRAD && BM <= 2 * (sizeof(T) == 2 ? CONV_BM_BF16 : CONV_BM_F32);
   const int mt = MULTI ? max(1, min(p.mt, p.tiles_m - tm0)) : 1;
-  // first operand image and row of m-tile tm
-  auto origin = [&](int tm, int& img0, int& y0) {
-    if (p.imgs > 1) {
-      img0 = tm * p.imgs;
-      y0 = 0;
-    } else {
-      const int tpi = SH / p.tr;
-      img0 = tm / tpi;
-      y0 = (tm - img0 * tpi) * p.tr;
-    }
+  // first operand image and row of the m-tile (wave-uniform; an image has tpi
+  // row tiles, or a tile has imgs images)
+  const int imgq = __builtin_amdgcn_readfirstlane(tm0 / p.tpi);
+  int img0 = imgq * p.imgs, y0 = (tm0 - imgq * p.tpi) * p.tr;
+  // its output rows are contiguous: m0 = (img0 * SH + y0) * SW on, and fewer
+  // than BM where whole rows and images do not fill the tile
+  auto rows_end = [&] {
+    return p.tpi == 1 ? min(img0 + p.imgs, p.Nb) * SH * SW : (img0 * SH + min(y0 + p.tr, SH)) * SW;
   };
-  int img0, y0;
-  origin(tm0, img0, y0);
   // halo offset of the first tap of each of this lane's MFMA rows
   int hbase[L::FM];
   {
-    const bool wo = !DGRAD && p.pool;  // window order: r = 4 * window + (dy, dx)
     const int per_row = wo ? SW >> 1 : SW, per_img = wo ? (p.tr >> 1) * per_row : p.tr * SW;
     const SmallDiv dimg(per_img, p.rc_img), drow(per_row, p.rc_row);
-    const int hr = p.hr, hc = p.hc, cs = p.cs;
+    const int hr = p.hr, hc = p.hc, cs = p.cs, rows = p.rows;
 #pragma unroll
     for (int i = 0; i < L::FM; ++i) {
-      const int r = L::arow(i), u = wo ? r >> 2 : r, d = r & 3;
+      const int ri = L::arow(i), r = ri < rows ? ri : 0, u = wo ? r >> 2 : r, d = r & 3;
       int rem, col;
       const int img = dimg.qr(u, rem), row = drow.qr(rem, col);
       const int y = wo ? 2 * row + (d >> 1) : row, x = wo ? 2 * col + (d & 1) : col;
@@ -2541,7 +2537,8 @@ __device__ __forceinline__ void halo_tile(const ConvProb& p, int local, char* sm
         const int q = (kb + 2) * CPB + cq;
         lb.template load<P>(q < nq ? qb[q] : -1);
       }
-      mma_halo<BM, BN, BK, NW>(sH, hbase, qa, kb * CPB, nq, sB + P * TL::B_ELEMS, acc);
+      if constexpr (sizeof(T) == 2) mma_halo_bf16<BM, BN, BK, NW>(sH, hbase, qa, kb * CPB, nq, sB + P * TL::B_ELEMS, acc);
+      else mma_halo_f32<BM, BN, BK, NW>(sH, hbase, qa, kb * CPB, nq, sB + P * TL::B_ELEMS, acc);
       if (kb + 1 < nkb) lb.template store<P ^ 1>(sB + (P ^ 1) * TL::B_ELEMS);
       __syncthreads();
     };
@@ -2594,7 +2591,7 @@ __device__ __forceinline__ void halo_tile(const ConvProb& p, int local, char* sm
     kloop(nq, (nq + CPB - 1) / CPB);
   }
   if constexpr (DGRAD) {
-    conv_dgrad_epilogue<T, BM, BN, L>(p, tm0 * BM, n0, acc, smem);
+    conv_dgrad_epilogue<T, BM, BN, L>(p, (img0 * SH + y0) * SW, rows_end(), n0, acc, smem);
   } else {
     // the epilogue, then any further m-tiles (mt > 1: one channel block, whose
     // tables stay in LDS). The k loop's last barrier has freed the staged
@@ -2606,16 +2603,20 @@ __device__ __forceinline__ void halo_tile(const ConvProb& p, int local, char* sm
       const bool more = MULTI && t < mt;
       u32x4 hv[HALO_PF];
       int hd[HALO_PF];
+      const int m0 = (img0 * SH + y0) * SW, m1 = rows_end();
       if (more) {
-        int nimg0, ny0;
-        origin(tm0 + t, nimg0, ny0);
-        fetch_halo<T, NT, HALO_PF>(p, nimg0, ny0, dcpt.r, hv, hd);
+        y0 += p.tr;
+        if (y0 >= SH) {
+          y0 = 0;
+          img0 += p.imgs;
+        }
+        fetch_halo<T, NT, HALO_PF>(p, img0, y0, dcpt.r, hv, hd);
         if (nkb > 2) {
           lb.template load<0>(col_of(cq, dcpt, nq, 0));
           lb.template load<1>(col_of(CPB + cq, dcpt, nq, 0));
         }
       }
-      conv_fwd_epilogue<T, L>(p, (tm0 + t - 1) * BM, n0, acc);
+      conv_fwd_epilogue<T, L>(p, m0, m1, n0, acc);
       if (!more) break;
       L::zero(acc);
       put_halo<T, HALO_PF>(sH, hv, hd);
@@ -2627,8 +2628,8 @@ __device__ __forceinline__ void halo_tile(const ConvProb& p, int local, char* sm
 }
 
 // Halo-tiled conv pass; each problem's tile shape (p.bm x p.bn) is the wide
-// BM x BN, the narrow 2BM x BN/2 or (bf16 forward only) the tall 4BM x BN/2 one,
-// so a launch mixes them. LDS is dynamic, sized
+// BM x BN, the narrow 2BM x BN/2, (bf16 forward only) the tall 4BM x BN/2 or
+// (fp32 only) the slim 4BM x BN/4 one, so a launch mixes them. LDS is dynamic, sized
 // by the host for the launch's largest staged block (small halos leave room
 // for more workgroups per CU).
 // Waves of a halo workgroup (bf16; fp32 keeps 4): a 4-wave workgroup runs
@@ -2646,6 +2647,8 @@ void conv_halo_kernel(const ConvProb* __restrict__ probs, const int32_t* __restr
   constexpr int NW = halo_waves<T>();
   if (p.bn == BN) {
     halo_tile<T, BM, BN, BK, DGRAD, NW>(p, local, smem);
+  } else if (sizeof(T) == 4 && p.bn == BN / 4) {
+    if constexpr (sizeof(T) == 4) halo_tile<T, 4 * BM, BN / 4, BK, DGRAD, NW>(p, local, smem);
   } else if (DGRAD || sizeof(T) != 2 || p.bm == 2 * BM) {
     halo_tile<T, 2 * BM, BN / 2, BK, DGRAD, NW>(p, local, smem);
   } else {

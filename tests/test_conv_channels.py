@@ -48,6 +48,25 @@ def test_against_the_oracle_and_alone(precision):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["f32", "bf16"])
+@pytest.mark.parametrize("side,batch", [(5, 40), (9, 3), (18, 7), (22, 5), (24, 9), (40, 2), (66, 2)])
+def test_row_tiles_that_rows_do_not_fill(precision, side, batch):
+    """Maps whose rows or images do not fill a tile, pooled with and without a
+    dropped last row and column, and maps wider than half a tile."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    specs = [{"layers": [C(c, 3, 1), R, POOL, C(40, 3, 1), R, C(8, 3, p), R] + ([POOL] if side > 9 else []) + [FLAT, L(10)],
+              "num_classes": 10} for c, p in ((16, 1), (72, 0))]
+    wl = W.Workload("rows", 2, batch, (3, side, side), precision, specs, 0.02, 1, 6, init="torch")
+    if side == 5:  # the second model's last map would be empty
+        wl.specs, wl.n_models = specs[:1], 1
+    m = list(range(wl.n_models))
+    orc, spread = run_oracle(wl, 1, m, spread=True)
+    print(compare_step(wl, run_gpu(wl, 1), orc, m, spread=spread))
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("kind", ["momentum", "adam"])
 def test_parameters_and_state_round_trip(kind):
     """What set_params / set_opt_state put in, get_* gives back, and a run
