@@ -1281,32 +1281,48 @@ __device__ __forceinline__ float opt_update1(const OptHp& h, float g, float w, f
   return w - h.lr * (m / (sqrtf(v) * h.isb2 + h.eps));
 }
 
-// Four consecutive elements (16-byte aligned state).
-__device__ __forceinline__ void opt_update4(const OptHp& h, const f32x4& g, f32x4& w, float* s1, float* s2) {
+// Loads and stores of the data an update touches once per step. NT
+// (non-temporal) for launches of large tiles: they pass hundreds of MB, and
+// the update data must not evict the operands from L2 (64 MLPs 816 us per step
+// without, 779 with). A launch of small tiles updates a few MB, which the
+// caches keep for the next step (12 bf16 MLPs with Adam 121.6 us with, 115.0
+// without).
+template <bool NT, class V> __device__ __forceinline__ V once_load(gptr<const V> p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool NT, class V> __device__ __forceinline__ void once_store(V v, gptr<V> p) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
+// Four consecutive elements, their state (a, v: as the kind has it) loaded by
+// the caller; the new state is stored here (16-byte aligned).
+template <bool NT>
+__device__ __forceinline__ void opt_update4(const OptHp& h, const f32x4& g, f32x4& w, f32x4 a, f32x4 v, float* s1,
+                                            float* s2) {
   if (h.kind == 0.f) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) w[e] = fmaf(-h.lr, g[e], w[e]);
     return;
   }
-  f32x4 a = __builtin_nontemporal_load((gptr<const f32x4>)s1);
   if (h.kind == 1.f) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       a[e] = fmaf(h.b1, a[e], g[e]);
       w[e] = fmaf(-h.lr, a[e], w[e]);
     }
-    __builtin_nontemporal_store(a, (gptr<f32x4>)s1);
+    once_store<NT>(a, (gptr<f32x4>)s1);
     return;
   }
-  f32x4 v = __builtin_nontemporal_load((gptr<const f32x4>)s2);
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     a[e] = fmaf(h.b1, a[e], h.c1 * g[e]);
     v[e] = fmaf(h.b2, v[e], h.c2 * g[e] * g[e]);
     w[e] = w[e] - h.lr * (a[e] / (sqrtf(v[e]) * h.isb2 + h.eps));
   }
-  __builtin_nontemporal_store(a, (gptr<f32x4>)s1);
-  __builtin_nontemporal_store(v, (gptr<f32x4>)s2);
+  once_store<NT>(a, (gptr<f32x4>)s1);
+  once_store<NT>(v, (gptr<f32x4>)s2);
 }
 
 // Column of element (r, c) in the GEMM epilogue's LDS tile: c XOR a multiple
@@ -1553,6 +1569,7 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
   using V = GemmVar<T, VAR>;
   using MM = typename V::MM;
   constexpr int BM = V::BM, BN = V::BN, BK = V::BK;
+  constexpr bool ONCE = VAR == GEMM_LARGE;  // update data touched once (non-temporal)
   __shared__ __attribute__((aligned(16))) char smem[V::BYTES];
   const int prob = tile_map[2 * blockIdx.x], local = tile_map[2 * blockIdx.x + 1];
   if (prob < 0) {
@@ -1606,6 +1623,7 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
   constexpr int CPR = BN / 4, NCH = BM * CPR / NT;  // epilogue float4 chunks per row, per thread
   const int ns = p.nsplit;
   f32x4 w0[NCH];  // master weights of the fused update (weight gradient only)
+  __shared__ OptHp s_hp[BWD && OPT ? BM : 1];  // OPT: each tile row's optimizer
   if constexpr (!BWD) {
     // row-major operands from column k0 on (a split's chunk, else 0), kc of them
     RowLoader<T, BM, BK, NT, D> la;
@@ -1625,10 +1643,7 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
     // the ones column of the bias gradient at n == nsplit. The fused
     // update's master-weight loads (this thread's float4 chunks of
     // W[m][n..n+3]) are issued at the start of the k loop's last block, so
-    // their latency overlaps that block and the staging below. Master
-    // weights, their bf16 copies and the optimizer state are touched once per
-    // step: they are loaded and stored non-temporally, so they do not evict
-    // the launch's reused operands from L2.
+    // their latency overlaps that block and the staging below.
     KRowLoader<T, BM, BK, NT, D, PAD> la;
     KRowLoader<T, BN, BK, NT, D, PAD> lb;
     const int bcol = p.bias_tile ? -1 : p.nsplit - n0;
@@ -1636,10 +1651,15 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
     lb.init((const T*)p.B + k0 * p.ldb, p.ldb, n0, kc, bcol >= 0 && bcol < BN ? bcol : -1);
     gemm_loop<T, BM, BN, BK, D, MM, OP_KMAJ, OP_KMAJ>(la, lb, nkb, (T*)smem, acc, [&] {
       if (p.epi != EPI_WGRAD) return;
+      if constexpr (OPT) {
+        // (two dependent loads, by the threads of the first BM rows only)
+        if ((int)threadIdx.x < BM && m0 + (int)threadIdx.x < p.M)
+          s_hp[threadIdx.x] = opt[p.row_model ? G(p.row_model)[m0 + threadIdx.x] : p.model];
+      }
 #pragma unroll
       for (int q = 0; q < NCH; ++q) {
         const int idx = threadIdx.x + NT * q, r = idx / CPR, n = n0 + (idx - r * CPR) * 4, m = m0 + r;
-        w0[q] = (m < p.M && n + 4 <= ns) ? __builtin_nontemporal_load((gptr<const f32x4>)(p.W + (int64_t)m * p.ldc + n))
+        w0[q] = (m < p.M && n + 4 <= ns) ? once_load<ONCE, f32x4>((gptr<const f32x4>)(p.W + (int64_t)m * p.ldc + n))
                                          : f32x4{0.f, 0.f, 0.f, 0.f};
       }
     });
@@ -1686,6 +1706,29 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
     });
   } else {
     MM::for_groups(acc, [&](int rl, int cl, float (&v)[4]) { stage(rl, cl, v); });
+  }
+  // The optimizer state of all of this thread's chunks, as far as the row's
+  // kind has it, in flight together behind the staging; not in the large bf16
+  // tiles, whose 64 registers it overflows (64 MLPs with Adam 1173 us per step
+  // chunk by chunk, 1503 so). Small tiles (waited for chunk by
+  // chunk, and with each row's optimizer looked up per chunk, 12 bf16 MLPs with
+  // Adam took 127 us per step; 121.6 so)
+  constexpr bool AHEAD = OPT && !(sizeof(T) == 2 && VAR == GEMM_LARGE);
+  f32x4 a1[AHEAD ? NCH : 1], a2[AHEAD ? NCH : 1];
+  if constexpr (BWD && AHEAD) {
+    if (epi == EPI_WGRAD) {
+#pragma unroll
+      for (int q = 0; q < NCH; ++q) {
+        const int idx = threadIdx.x + NT * q, r = idx / CPR, n = n0 + (idx - r * CPR) * 4, m = m0 + r;
+        a1[q] = a2[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (m < p.M && n + 4 <= ns) {
+          const float kind = s_hp[r].kind;
+          const int64_t base = (int64_t)m * p.ldc + n;
+          if (kind != 0.f) a1[q] = once_load<ONCE, f32x4>((gptr<const f32x4>)(p.s1 + base));
+          if (kind == 2.f) a2[q] = once_load<ONCE, f32x4>((gptr<const f32x4>)(p.s2 + base));
+        }
+      }
+    }
   }
   __syncthreads();
 
@@ -1736,8 +1779,7 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
     const int idx = threadIdx.x + NT * q, r = idx / CPR, cc = idx - r * CPR;
     const int m = m0 + r, n = n0 + cc * 4;
     if (m >= p.M || n > ns) continue;
-    // this row's model: its own optimizer, or its own rate (staged in s_lr)
-    const int mdl = OPT ? (p.row_model ? p.row_model[m] : p.model) : 0;
+    // this row's model: its own optimizer (s_hp), or its own rate (s_lr)
     const float lr_m = (!OPT && lrv) ? s_lr[r] : lr;
     float* s = sC + r * CLD + sc_col<BN>(r, cc * 4);
     const int64_t base = (int64_t)m * p.ldc + n;
@@ -1747,17 +1789,25 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
       f32x4 w;
       if constexpr (OPT) {
         w = w0[q];
-        opt_update4(opt[mdl], g, w, p.s1 + base, p.s2 + base);
+        if constexpr (AHEAD) {
+          opt_update4<ONCE>(s_hp[r], g, w, a1[q], a2[q], p.s1 + base, p.s2 + base);
+        } else {
+          const float kind = s_hp[r].kind;
+          f32x4 b1 = {0.f, 0.f, 0.f, 0.f}, b2 = b1;
+          if (kind != 0.f) b1 = once_load<ONCE, f32x4>((gptr<const f32x4>)(p.s1 + base));
+          if (kind == 2.f) b2 = once_load<ONCE, f32x4>((gptr<const f32x4>)(p.s2 + base));
+          opt_update4<ONCE>(s_hp[r], g, w, b1, b2, p.s1 + base, p.s2 + base);
+        }
       } else {
         w = f32x4{fmaf(-lr_m, g[0], w0[q][0]), fmaf(-lr_m, g[1], w0[q][1]), fmaf(-lr_m, g[2], w0[q][2]),
                   fmaf(-lr_m, g[3], w0[q][3])};
       }
-      __builtin_nontemporal_store(w, (gptr<f32x4>)(p.W + base));
+      once_store<ONCE>(w, (gptr<f32x4>)(p.W + base));
       if (p.Wb) {
         u32x2 hb;
         hb[0] = f2bf2(w[0], w[1]);
         hb[1] = f2bf2(w[2], w[3]);
-        __builtin_nontemporal_store(hb, (gptr<u32x2>)((bf16_t*)p.Wb + base));
+        once_store<ONCE>(hb, (gptr<u32x2>)((bf16_t*)p.Wb + base));
       }
     } else {
       for (int e = 0; e < 4 && n + e <= ns && n + e < p.N; ++e) {
@@ -1765,13 +1815,13 @@ void gemm_kernel(const GemmProb* __restrict__ probs,
         if (n + e < ns) {
           if (keep_grads) ((float*)p.C)[base + e] = g;
           float w;
-          if constexpr (OPT) w = opt_update1(opt[mdl], g, p.W[base + e], p.s1 + base + e, p.s2 + base + e);
+          if constexpr (OPT) w = opt_update1(s_hp[r], g, p.W[base + e], p.s1 + base + e, p.s2 + base + e);
           else w = fmaf(-lr_m, g, p.W[base + e]);
           p.W[base + e] = w;
           if (p.Wb) ((bf16_t*)p.Wb)[base + e] = f2bf(w);
         } else {
           if (keep_grads) p.dbias[m] = g;
-          if constexpr (OPT) p.bmaster[m] = opt_update1(opt[mdl], g, p.bmaster[m], p.sb1 + m, p.sb2 + m);
+          if constexpr (OPT) p.bmaster[m] = opt_update1(s_hp[r], g, p.bmaster[m], p.sb1 + m, p.sb2 + m);
           else p.bmaster[m] = fmaf(-lr_m, g, p.bmaster[m]);
         }
       }
