@@ -196,10 +196,12 @@ struct AttnProb {
   float scale;
 };
 
-// LDS of one workgroup: Q, K, V (and dA) in the storage type (es bytes per
-// element) as rows of d plus one 16-byte chunk, and one (two) T x (T + 1)
-// fp32 score tiles. The parser's bound takes es = 4.
+// LDS of one workgroup. fp32: Q, K, V (and dA) as rows of d plus one 16-byte
+// chunk, and one (two) T x (T + 1) score tiles. bf16: V (K, Q and dA, and 64
+// row sums) as T + 1 rows of d + 16 elements. The parser's bound of 160 KiB
+// takes the fp32 form; no shape within it exceeds it in bf16.
 inline size_t attn_lds_bytes(int T, int d, bool bwd, int es) {
+  if (es == 2) return (size_t)(bwd ? 3 : 1) * (T + 1) * (d + 16) * 2 + (bwd ? 64 * 4 : 0);
   return (size_t)(bwd ? 4 : 3) * T * (d + 16 / es) * es + (size_t)(bwd ? 2 : 1) * T * (T + 1) * 4;
 }
 

@@ -3154,11 +3154,11 @@ __global__ __launch_bounds__(CE_ROWS * CE_LANES) void ce_rows_kernel(const CePro
 
 // ---------------------------------------------------------------------------
 // Self-attention core (AttnProb), one workgroup of 256 threads per (problem,
-// sample). The sample's Q, K, V (and dA) rows are staged in LDS as fp32 with
-// rows padded to d + 1 floats; every output element is one fmaf chain over
-// its contraction index in ascending order, and the softmax row reductions
-// are fixed lane-shuffle butterflies, so the result depends on nothing but
-// the sample's own values.
+// sample); the result depends on nothing but the sample's own values.
+// fp32 storage: the sample's Q, K, V (and dA) rows are staged in LDS, every
+// output element is one fmaf chain over its contraction index in ascending
+// order, and the softmax row reductions are fixed lane-shuffle butterflies.
+// (bf16 storage: attn_fwd_mfma_kernel, attn_bwd_mfma_kernel below.)
 // ---------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ void attn_stage(const AttnProb& p, int b, T* sQ, T* sK, T* sV) {
@@ -3340,6 +3340,294 @@ __global__ __launch_bounds__(256) void attn_bwd_kernel(const AttnProb* __restric
                       [&](int r, int k0, const float* v, int n) {
                         attn_put4<T>(dqkv + (int64_t)r * p.ldq + 2 * d + k0, v, n, 1.f);
                       });
+}
+
+// bf16 storage: the same products on v_mfma_f32_16x16x32_bf16. They are 16 to
+// 64 tokens wide, far too small to be bound by anything but latency, so the
+// kernels keep the chain short: the T x T products take their operands straight
+// from global memory (16 bytes per lane), softmax and its backward stay in the
+// accumulator registers, and those registers are the next product's operand as
+// they are, because the contraction index may be numbered freely as long as
+// both operands agree: element e of lane group g stands for token
+// 16 * (e / 4) + 4 g + e % 4 of a 32-token step, which is where the
+// accumulators of two 16-token tiles have it. The other operand comes from LDS
+// rows [token][d] through transpose reads. P and dS are fp32: each is split
+// exactly into three bf16 terms (24 bits), whose products with bf16 values are
+// exact in fp32, so nothing is rounded that the fmaf chains did not round.
+// A 16-token strip of queries (backward also: of keys) belongs to 4, 2 or 1 of
+// the four waves (1, 2, more strips), which share the columns of its products.
+// Against the fmaf chains on LDS tiles (attn8: 32 tokens of 64 or 128, 8 x 128
+// and 3 x 128 samples per launch): forward 21.7 and 17.4 -> 10.3 and 6.8 us,
+// backward 44.6 and 25.2 -> 19.8 and 13.6 us, step 353 -> 296 us.
+__device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ bf16x8 as_bf8(const u32x4& v) { return __builtin_bit_cast(bf16x8, v); }
+
+// LDS rows [token][d + 16], row Tn zero: a step's tokens past Tn read it.
+__device__ __forceinline__ int attn_ld(int d) { return d + 16; }
+__device__ __forceinline__ void attn_stage_rows(bf16_t* s, const bf16_t* src, int64_t ld, int Tn, int d) {
+  const int vpr = d >> 3, ls = attn_ld(d);
+  for (int e = threadIdx.x; e < (Tn + 1) * vpr; e += 256) {
+    const int t = e / vpr, j = (e - t * vpr) << 3;
+    *(u32x4*)(s + t * ls + j) = t < Tn ? *(gptr<const u32x4>)(src + (int64_t)t * ld + j) : zero4();
+  }
+}
+
+// Operand rows from global memory: lane r = lane % 16 holds columns
+// kk + 8 (lane / 16) .. + 7 of row row0 + r (the last row where that is past it).
+struct AttnRows {
+  gptr<const bf16_t> row;
+  int d;
+  __device__ __forceinline__ AttnRows(const bf16_t* base, int64_t ld, int row0, int Tn, int d_) : d(d_) {
+    const int lane = threadIdx.x & 63;
+    row = G(base + (int64_t)min(row0 + (lane & 15), Tn - 1) * ld + 8 * (lane >> 4));
+  }
+  __device__ __forceinline__ bf16x8 at(int kk) const {
+    const int k = kk + 8 * (int)((threadIdx.x & 63) >> 4);
+    return as_bf8(k < d ? *(gptr<const u32x4>)(row + kk) : zero4());
+  }
+};
+
+// out[n] = sum over the d columns of a[n]'s rows times b's: NS tiles of 16 x 16
+// (rows of a[n] down, rows of b across), KS steps of 32 columns in flight.
+template <int NS>
+__device__ __forceinline__ void attn_dots(const AttnRows (&a)[NS], const AttnRows& b, int d, f32x4 (&out)[NS]) {
+  constexpr int KS = NS <= 2 ? 4 : 2;
+#pragma unroll
+  for (int n = 0; n < NS; ++n) out[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int kk = 0; kk < d; kk += 32 * KS) {
+    bf16x8 fb[KS], fa[NS][KS];
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      fb[k] = b.at(kk + 32 * k);
+#pragma unroll
+      for (int n = 0; n < NS; ++n) fa[n][k] = a[n].at(kk + 32 * k);
+    }
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
+#pragma unroll
+      for (int n = 0; n < NS; ++n) out[n] = mfma16(fa[n][k], fb[k], out[n]);
+  }
+}
+
+// The three bf16 terms of x[0..7], exact: x = t[0] + t[1] + t[2].
+__device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
+  float r[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) r[e] = x[e];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    u32x4 w;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t v = f2bf2(r[2 * q], r[2 * q + 1]);
+      w[q] = v;
+      r[2 * q] -= __uint_as_float(v << 16);
+      r[2 * q + 1] -= __uint_as_float(v & 0xffff0000u);
+    }
+    t[j] = as_bf8(w);
+  }
+}
+
+// dst[token][c] = scale * sum over x of s[x][c] * m[x][token] for the strip of
+// 16 tokens whose m is in the accumulator layout (m[n][r] of lane: x = 16 n +
+// 4 (lane / 16) + r, token lane % 16; zero past the last x) and every H-th
+// 16-column tile from h; s: LDS rows [x][ls], row Tn zero. Four consecutive
+// columns per lane and store.
+template <int NS>
+__device__ __forceinline__ void attn_apply(const f32x4 (&m)[NS], const bf16_t* s, int ls, int Tn, int d, int h, int H,
+                                           bool in, bf16_t* dst, float scale) {
+  constexpr int STEPS = (NS + 1) / 2;
+  const int lane = threadIdx.x & 63, g = lane >> 4, a = lane & 15;
+  bf16x8 t[STEPS][3];
+  int row[STEPS][2];
+#pragma unroll
+  for (int k = 0; k < STEPS; ++k) {
+    float x[8];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      x[r] = m[2 * k][r];
+      x[4 + r] = 2 * k + 1 < NS ? m[2 * k + 1 < NS ? 2 * k + 1 : 0][r] : 0.f;
+    }
+    split3(x, t[k]);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) row[k][q] = min(32 * k + 16 * q + 4 * g + (a >> 2), Tn) * ls + 4 * (a & 3);
+  }
+  typedef short s4 __attribute__((ext_vector_type(4)));
+  for (int c = 16 * h; c < d; c += 16 * H) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) {
+      const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4*)(s + row[k][0] + c)));
+      const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4*)(s + row[k][1] + c)));
+      const bf16x8 f = as_bf8(u32x4{lo[0], lo[1], hi[0], hi[1]});
+#pragma unroll
+      for (int j = 2; j >= 0; --j) acc = mfma16(f, t[k][j], acc);  // the small terms first
+    }
+    if (in && c + 4 * g < d) {
+      u32x2 w;
+      w[0] = f2bf2(acc[0] * scale, acc[1] * scale);
+      w[1] = f2bf2(acc[2] * scale, acc[3] * scale);
+      *(gptr<u32x2>)(dst + c + 4 * g) = w;
+    }
+  }
+}
+
+// Four consecutive probabilities of a row (t .. t + 3, those below Tn).
+__device__ __forceinline__ void attn_load_p(const float* row, int t, int Tn, f32x4& v) {
+  if ((Tn & 3) == 0) {
+    v = t < Tn ? *(gptr<const f32x4>)(row + t) : f32x4{0.f, 0.f, 0.f, 0.f};
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = t + r < Tn ? G(row)[t + r] : 0.f;
+  }
+}
+
+template <int NS>
+__device__ __forceinline__ void attn_fwd_strips(const AttnProb& p, int b, bf16_t* sV) {
+  constexpr int H = NS == 1 ? 4 : NS == 2 ? 2 : 1;
+  const int Tn = p.T, d = p.d, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4;
+  const int strip = wave / H, h = wave % H;
+  const bool live = strip < NS;
+  const bf16_t* q = (const bf16_t*)p.QKV + (int64_t)b * Tn * p.ldq;
+  const int i = 16 * strip + (lane & 15);
+  attn_stage_rows(sV, q + 2 * d, p.ldq, Tn, d);
+  f32x4 s[NS];
+  if (live) {
+    const auto rows = [&](int n) { return AttnRows(q + d, p.ldq, 16 * n, Tn, d); };
+    const AttnRows qr(q, p.ldq, 16 * strip, Tn, d);
+    if constexpr (NS == 1) attn_dots<NS>({rows(0)}, qr, d, s);
+    else if constexpr (NS == 2) attn_dots<NS>({rows(0), rows(1)}, qr, d, s);
+    else if constexpr (NS == 3) attn_dots<NS>({rows(0), rows(1), rows(2)}, qr, d, s);
+    else attn_dots<NS>({rows(0), rows(1), rows(2), rows(3)}, qr, d, s);
+    // softmax over the keys of query i: the lane's own, then lanes 16 and 32 on
+    float mx = -INFINITY;
+#pragma unroll
+    for (int n = 0; n < NS; ++n)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        s[n][r] = 16 * n + 4 * g + r < Tn ? s[n][r] * p.scale : -INFINITY;
+        mx = fmaxf(mx, s[n][r]);
+      }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    float sum = 0.f;
+#pragma unroll
+    for (int n = 0; n < NS; ++n)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        s[n][r] = 16 * n + 4 * g + r < Tn ? expf(s[n][r] - mx) : 0.f;
+        sum += s[n][r];
+      }
+    sum += __shfl_xor(sum, 16, 64);
+    sum += __shfl_xor(sum, 32, 64);
+    const float inv = 1.0f / sum;
+    float* prow = p.P + ((int64_t)b * Tn + i) * Tn;
+#pragma unroll
+    for (int n = 0; n < NS; ++n) {
+      const int t = 16 * n + 4 * g;
+      s[n] *= inv;
+      if (h == 0 && i < Tn && t < Tn) {
+        if ((Tn & 3) == 0) *(gptr<f32x4>)(prow + t) = s[n];
+        else
+          for (int r = 0; r < 4 && t + r < Tn; ++r) G(prow)[t + r] = s[n][r];
+      }
+    }
+  }
+  __syncthreads();
+  if (live)
+    attn_apply<NS>(s, sV, attn_ld(d), Tn, d, h, H, i < Tn, (bf16_t*)p.A + ((int64_t)b * Tn + min(i, Tn - 1)) * p.lda, 1.f);
+}
+
+__global__ __launch_bounds__(256) void attn_fwd_mfma_kernel(const AttnProb* __restrict__ probs,
+                                                            const int32_t* __restrict__ tile_map) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int pi = tile_map[2 * blockIdx.x], b = tile_map[2 * blockIdx.x + 1];
+  if (pi < 0) return;
+  const AttnProb& p = probs[pi];
+  switch ((p.T + 15) >> 4) {
+    case 1: return attn_fwd_strips<1>(p, b, (bf16_t*)smem);
+    case 2: return attn_fwd_strips<2>(p, b, (bf16_t*)smem);
+    case 3: return attn_fwd_strips<3>(p, b, (bf16_t*)smem);
+    default: return attn_fwd_strips<4>(p, b, (bf16_t*)smem);
+  }
+}
+
+template <int NS>
+__device__ __forceinline__ void attn_bwd_strips(const AttnProb& p, int b, char* smem) {
+  constexpr int H = NS == 1 ? 4 : NS == 2 ? 2 : 1;
+  const int Tn = p.T, d = p.d, ls = attn_ld(d), wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4;
+  const int strip = wave / H, h = wave % H, c16 = 16 * strip + (lane & 15);
+  const bool live = strip < NS, in = c16 < Tn;
+  float* sD = (float*)smem;  // row sums of P * dP
+  bf16_t* sK = (bf16_t*)(sD + 64);
+  bf16_t* sQ = sK + (Tn + 1) * ls;
+  bf16_t* sG = sQ + (Tn + 1) * ls;  // dA
+  const bf16_t* q = (const bf16_t*)p.QKV + (int64_t)b * Tn * p.ldq;
+  const bf16_t* dA = (const bf16_t*)p.dA + (int64_t)b * Tn * p.lda;
+  const float* Pg = p.P + (int64_t)b * Tn * Tn;
+  bf16_t* dst = (bf16_t*)p.dQKV + ((int64_t)b * Tn + min(c16, Tn - 1)) * p.ldq;
+  attn_stage_rows(sK, q + d, p.ldq, Tn, d);
+  attn_stage_rows(sQ, q, p.ldq, Tn, d);
+  attn_stage_rows(sG, dA, p.lda, Tn, d);
+  const auto vr = [&](int n) { return AttnRows(q + 2 * d, p.ldq, 16 * n, Tn, d); };
+  const auto gr = [&](int n) { return AttnRows(dA, p.lda, 16 * n, Tn, d); };
+  const auto dots = [&](const auto& rows, const AttnRows& o, f32x4 (&out)[NS]) {
+    if constexpr (NS == 1) attn_dots<NS>({rows(0)}, o, d, out);
+    else if constexpr (NS == 2) attn_dots<NS>({rows(0), rows(1)}, o, d, out);
+    else if constexpr (NS == 3) attn_dots<NS>({rows(0), rows(1), rows(2)}, o, d, out);
+    else attn_dots<NS>({rows(0), rows(1), rows(2), rows(3)}, o, d, out);
+  };
+  f32x4 ds[NS], pt[NS];
+  if (live) {
+    // query c16 across, keys down: dP, its row sum, dS
+    dots(vr, gr(strip), ds);
+    float rd = 0.f;
+#pragma unroll
+    for (int n = 0; n < NS; ++n) {
+      attn_load_p(Pg + (int64_t)min(c16, Tn - 1) * Tn, 16 * n + 4 * g, Tn, pt[n]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) rd = fmaf(pt[n][r], ds[n][r], rd);
+    }
+    rd += __shfl_xor(rd, 16, 64);
+    rd += __shfl_xor(rd, 32, 64);
+    if (g == 0 && h == 0 && in) sD[c16] = rd;
+#pragma unroll
+    for (int n = 0; n < NS; ++n)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) ds[n][r] = pt[n][r] * (ds[n][r] - rd);
+  }
+  __syncthreads();
+  if (!live) return;
+  attn_apply<NS>(ds, sK, ls, Tn, d, h, H, in, dst, p.scale);  // dQ
+  // key c16 across, queries down: dP again, P and dS by column
+  dots(gr, vr(strip), ds);
+#pragma unroll
+  for (int n = 0; n < NS; ++n)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 16 * n + 4 * g + r;
+      const bool ok = i < Tn && in;
+      pt[n][r] = ok ? G(Pg)[i * Tn + c16] : 0.f;
+      ds[n][r] = ok ? pt[n][r] * (ds[n][r] - sD[i]) : 0.f;
+    }
+  attn_apply<NS>(ds, sQ, ls, Tn, d, h, H, in, dst + d, p.scale);    // dK
+  attn_apply<NS>(pt, sG, ls, Tn, d, h, H, in, dst + 2 * d, 1.f);    // dV
+}
+
+__global__ __launch_bounds__(256) void attn_bwd_mfma_kernel(const AttnProb* __restrict__ probs,
+                                                            const int32_t* __restrict__ tile_map) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int pi = tile_map[2 * blockIdx.x], b = tile_map[2 * blockIdx.x + 1];
+  if (pi < 0) return;
+  const AttnProb& p = probs[pi];
+  switch ((p.T + 15) >> 4) {
+    case 1: return attn_bwd_strips<1>(p, b, smem);
+    case 2: return attn_bwd_strips<2>(p, b, smem);
+    case 3: return attn_bwd_strips<3>(p, b, smem);
+    default: return attn_bwd_strips<4>(p, b, smem);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -3565,9 +3853,9 @@ hipError_t launch_attn(bool bf16, bool bwd, const AttnProb* probs, const int32_t
   // allow dynamic LDS up to the whole 160 KiB of a CU (above the default cap)
   static const hipError_t attr = [] {
     hipError_t e = hipSuccess, r;
-    const void* k[4] = {reinterpret_cast<const void*>(&attn_fwd_kernel<bf16_t>),
+    const void* k[4] = {reinterpret_cast<const void*>(&attn_fwd_mfma_kernel),
                         reinterpret_cast<const void*>(&attn_fwd_kernel<float>),
-                        reinterpret_cast<const void*>(&attn_bwd_kernel<bf16_t>),
+                        reinterpret_cast<const void*>(&attn_bwd_mfma_kernel),
                         reinterpret_cast<const void*>(&attn_bwd_kernel<float>)};
     for (const void* f : k) {
       r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -3578,12 +3866,12 @@ hipError_t launch_attn(bool bf16, bool bwd, const AttnProb* probs, const int32_t
   if (attr != hipSuccess) return attr;
   if (bwd) {
     if (bf16)
-      hipLaunchKernelGGL(attn_bwd_kernel<bf16_t>, dim3(nblocks), dim3(256), lds_bytes, s, probs, tile_map);
+      hipLaunchKernelGGL(attn_bwd_mfma_kernel, dim3(nblocks), dim3(256), lds_bytes, s, probs, tile_map);
     else
       hipLaunchKernelGGL(attn_bwd_kernel<float>, dim3(nblocks), dim3(256), lds_bytes, s, probs, tile_map);
   } else {
     if (bf16)
-      hipLaunchKernelGGL(attn_fwd_kernel<bf16_t>, dim3(nblocks), dim3(256), lds_bytes, s, probs, tile_map);
+      hipLaunchKernelGGL(attn_fwd_mfma_kernel, dim3(nblocks), dim3(256), lds_bytes, s, probs, tile_map);
     else
       hipLaunchKernelGGL(attn_fwd_kernel<float>, dim3(nblocks), dim3(256), lds_bytes, s, probs, tile_map);
   }

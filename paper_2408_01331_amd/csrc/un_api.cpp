@@ -452,7 +452,7 @@ un_status parse_model(const un_model_spec& s, const un_input_spec& in, int mi, M
         return UN_ERR_INVALID;
       }
       const int d = c;
-      const size_t lds = attn_lds_bytes(seq, d, true, 4);  // the fp32 layout, the larger one
+      const size_t lds = attn_lds_bytes(seq, d, true, 4);  // the fp32 layout, for both precisions
       if (seq > 64 || lds > (size_t)160 * 1024) {
         why = where(i) + "attention supports up to 64 tokens whose working set fits 160 KiB of LDS";
         return UN_ERR_UNSUPPORTED;

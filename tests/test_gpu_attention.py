@@ -107,3 +107,19 @@ def test_attention_workload_all_models():
     orc, spread = run_oracle(wl, 3, m, spread=True)
     rep = compare_run(wl, run_gpu(wl, 3), orc, m, spread=spread)
     print(f"[{wl.name} 3 steps] " + ", ".join(f"{k}={v:.3g}" for k, v in rep.items()), flush=True)
+
+
+@pytest.mark.parametrize("precision", ["f32", "bf16"])
+@pytest.mark.parametrize("T,d", [(1, 8), (7, 24), (15, 40), (16, 16), (17, 136), (32, 72), (33, 8), (48, 24), (50, 64), (64, 120)])
+def test_core_tile_edges(precision, T, d):
+    """Token counts at the edges of the core's 16-token strips and 32-token
+    steps, rows that are no whole float4s, and widths that are no whole column
+    tiles; two models so that a launch mixes strip counts."""
+    _need_gpu()
+    specs = [{"layers": [("unflatten", T), ("attention",), ("flatten",), ("linear", 10)], "num_classes": 10},
+             {"layers": [("linear", 64), ("relu",), ("unflatten", 4), ("attention",), ("flatten",), ("linear", 10)],
+              "num_classes": 10}]
+    wl = W.Workload("core", 2, 3, (T * d,), precision, specs, 0.02, 1, 8, init="torch")
+    m = [0, 1]
+    orc, spread = run_oracle(wl, 1, m, spread=True)
+    print(compare_step(wl, run_gpu(wl, 1), orc, m, spread=spread))
