@@ -300,8 +300,9 @@ hipError_t launch_conv_fwd(bool bf16, const ConvProb* probs, const int32_t* tile
                            hipStream_t s);
 hipError_t launch_conv_dgrad(bool bf16, const ConvProb* probs, const int32_t* tile_map, int ntiles,
                              hipStream_t s);
-// mode: 0 any layer; 1 pooled, 2 unpooled, both with O and C whole 16-byte vectors
-hipError_t launch_conv_wgrad(bool bf16, int mode, const ConvProb* probs, const int32_t* tile_map, int ntiles,
+// mode: 0 any layer; 1 pooled, 2 unpooled, both with O and C whole 16-byte
+// vectors and bm (conv_wg_rows) channels per tile
+hipError_t launch_conv_wgrad(bool bf16, int mode, int bm, const ConvProb* probs, const int32_t* tile_map, int ntiles,
                              int64_t wsoff, hipStream_t s);
 // Halo-tiled forward (dgrad = false) or data gradient (dgrad = true); every
 // problem of the launch has halo != 0 (either tile shape).
@@ -341,9 +342,9 @@ constexpr GemmTile gemm_tile(bool bf16, int variant) {
 constexpr int GEMM_BK_BF16 = 64, GEMM_BK_F32 = 32;
 constexpr int CONV_BM_BF16 = 128, CONV_BN_BF16 = 128, CONV_BK_BF16 = 64;
 constexpr int CONV_BM_F32 = 64, CONV_BN_F32 = 64, CONV_BK_F32 = 32;
-// bf16 conv weight gradients whose blocks all have at most this many output
-// channels run 64-row tiles (launch mode bit WG_NARROW_BIT)
-constexpr int CONV_WG_NARROW_BM = 64, WG_NARROW_BIT = 4;
+// output channels per tile of a whole-vector conv weight-gradient launch whose
+// blocks have at most maxO: the smallest that holds them, up to the largest tile
+constexpr int conv_wg_rows(bool bf16, int maxO) { return bf16 ? (maxO <= 64 ? 64 : 128) : maxO <= 16 ? 16 : maxO <= 32 ? 32 : 64; }
 constexpr int SGD_TILE = 64;
 constexpr int REDUCE_BLOCK = 256;
 constexpr int CE_MAX_BATCH = 1 << 20;

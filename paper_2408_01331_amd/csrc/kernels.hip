@@ -46,13 +46,20 @@
 // chunk c of row k at c ^ 4*(k % 4); 64-element rows (two rows per 256 bytes
 // of banks) at c ^ 4*((k / 2) % 2). With padded rows instead (stride of 8
 // banks) the same reads measured twice the LDS cycles (SQ_LDS_BANK_CONFLICT
-// half of SQ_LDS_IDX_ACTIVE). fp32: rows padded by 8 elements.
-constexpr int KMAJ_PAD_BF16 = 0, KMAJ_PAD_F32 = 8;
+// half of SQ_LDS_IDX_ACTIVE). fp32: rows padded by 4 elements, so that the four
+// rows k, k + 4, .. that a wave reads 16 columns of start 16 banks apart.
+constexpr int KMAJ_PAD_BF16 = 0, KMAJ_PAD_F32 = 4;
 template <int LDR>
 __device__ __forceinline__ int kmaj_bf16(int k, int col) {
   static_assert(LDR % 128 == 0 || LDR == 64, "rows of 64 or a multiple of 128 elements");
   const int x = LDR == 64 ? ((k >> 1) & 1) << 2 : (k & 3) << 2;
   return k * LDR + (((col >> 3) ^ x) << 3) + (col & 7);
+}
+// element (k, col) of either type's k-major stage
+template <typename T, int LDR>
+__device__ __forceinline__ int kmaj_off(int k, int col) {
+  if constexpr (sizeof(T) == 2) return kmaj_bf16<LDR>(k, col);
+  else return k * LDR + col;
 }
 #ifndef UN_HALO_WAVES
 #define UN_HALO_WAVES 8
@@ -348,19 +355,20 @@ struct GemmMma<bf16_t, BM, BN, BK, WGM_, WGN_> {
 
 template <int BM, int BN, int BK, int WGM_, int WGN_>
 struct GemmMma<float, BM, BN, BK, WGM_, WGN_> {
-  using TL = Tile<float, BM, BN, BK>;
-  static constexpr int NT = 256;
-  static constexpr int LDK = TL::LDK;
+  static constexpr int WGM = WGM_, WGN = WGN_, NT = 64 * WGM * WGN;
+  static constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 16, FN = WN / 16;
+  static_assert(FM >= 1 && FN >= 1, "wave tile smaller than one 16x16 block");
+  static constexpr int LDK = Tile<float, 64, 64, BK>::LDK;
   static constexpr int LDR_A = BM + KMAJ_PAD_F32, LDR_B = BN + KMAJ_PAD_F32;
   static constexpr int CLD = BN + 4;
   static constexpr int A_ELEMS = BM * LDK > BK * LDR_A ? BM * LDK : BK * LDR_A;  // one stage of either layout
   static constexpr int B_ELEMS = BN * LDK > BK * LDR_B ? BN * LDK : BK * LDR_B;
-  using Acc = f32x4[TL::FM][TL::FN];
+  using Acc = f32x4[FM][FN];
   __device__ __forceinline__ static void zero(Acc& acc) {
 #pragma unroll
-    for (int i = 0; i < TL::FM; ++i)
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
-      for (int j = 0; j < TL::FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   // Lane (r = lane % 16, g = lane / 16) feeds k = kk + 4g + q to the q-th
   // 16x16x4 MFMA: its four values of tile row row0 + r.
@@ -373,31 +381,31 @@ struct GemmMma<float, BM, BN, BK, WGM_, WGN_> {
   template <int AM, int BMODE>
   __device__ __forceinline__ static void block(const float* sA, const float* sB, Acc& acc) {
     const int wave = threadIdx.x >> 6;
-    const int wm = (wave >> 1) * TL::WM, wn = (wave & 1) * TL::WN;
+    const int wm = (wave / WGN) * WM, wn = (wave % WGN) * WN;
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 16) {
-      f32x4 a[TL::FM], b[TL::FN];
+      f32x4 a[FM], b[FN];
 #pragma unroll
-      for (int i = 0; i < TL::FM; ++i) a[i] = frag<AM, LDR_A>(sA, wm + 16 * i, kk);
+      for (int i = 0; i < FM; ++i) a[i] = frag<AM, LDR_A>(sA, wm + 16 * i, kk);
 #pragma unroll
-      for (int j = 0; j < TL::FN; ++j) b[j] = frag<BMODE, LDR_B>(sB, wn + 16 * j, kk);
+      for (int j = 0; j < FN; ++j) b[j] = frag<BMODE, LDR_B>(sB, wn + 16 * j, kk);
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int i = 0; i < TL::FM; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-          for (int j = 0; j < TL::FN; ++j)
+          for (int j = 0; j < FN; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][q], b[j][q], acc[i][j], 0, 0, 0);
     }
   }
   template <class F>
   __device__ __forceinline__ static void for_groups(const Acc& acc, F&& f) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = (wave >> 1) * TL::WM, wn = (wave & 1) * TL::WN;
+    const int wm = (wave / WGN) * WM, wn = (wave % WGN) * WN;
 #pragma unroll
-    for (int i = 0; i < TL::FM; ++i)
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
-      for (int j = 0; j < TL::FN; ++j) {
+      for (int j = 0; j < FN; ++j) {
         float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
         f(wm + 16 * i + 4 * (lane >> 4), wn + 16 * j + (lane & 15), v);
       }
@@ -927,33 +935,24 @@ __device__ __forceinline__ void microtile_of(int t, int& rg, int& pg) {
 }
 
 // Weight-gradient operands of one k-block (BK output pixels), both written to
-// LDS as [row][pixel]: threads 0..127 build A, rows = output channel o, from
-// dZ (the pooled gradient G[w][o], already ReLU'-masked, and the window
-// argmax); threads 128..255 build B, rows = j = (u, v, c) plus the bias column
-// j == KH*KW*C reading 1, from the input patch in NHWC X. load() only issues
-// the global loads into a register slot; the argmax selection, the transpose
-// and the LDS writes happen in store(), after the current k-block's products,
-// so the loads overlap them. Both roles share the register slots.
-// MODE selects the code compiled into the k-loop (a loop body holding every
-// path overflows the instruction cache): WG_POOLED / WG_PLAIN for a pooled /
-// unpooled block whose channel counts O and C are whole 16-byte vectors,
-// WG_GENERIC for anything else (element by element where needed).
-enum { WG_GENERIC = 0, WG_POOLED = 1, WG_PLAIN = 2, WG_NARROW = WG_NARROW_BIT };
+// LDS as [row][pixel], for channel counts that are no whole 16-byte vectors
+// (models whose channels cannot be stored padded): threads 0..127 build A,
+// rows = output channel o, from dZ (the pooled gradient G[w][o], already
+// ReLU'-masked, and the window argmax); threads 128..255 build B, rows = j =
+// (u, v, c) plus the bias column j == KH*KW*C reading 1, from the input patch
+// in NHWC X; element by element, pooled or not. The transpose and the LDS
+// writes happen in store(), after the current k-block's products.
+enum { WG_GENERIC = 0, WG_POOLED = 1, WG_PLAIN = 2 };
 
-template <typename T, int BM, int BN, int BK, int MODE>
+template <typename T, int BM, int BN, int BK>
 struct WgradLoader {
-  static constexpr int VEC = TT<T>::VEC, NW = VEC / 4, LDK = BK + UN_LDS_PAD_CHUNKS * VEC;
-  static constexpr int OOB = 0x7ffffff0;  // a buffer offset past every range: the load returns zero
-  static constexpr bool POOL = MODE == WG_POOLED;
+  static constexpr int VEC = TT<T>::VEC, LDK = BK + UN_LDS_PAD_CHUNKS * VEC;
   static_assert(BM / VEC == 16 && BN / VEC == 16 && BK / VEC == 8, "16 x 8 micro-tiles per operand");
-  static_assert(VEC % 4 == 0, "a micro-tile holds whole 2x2 windows");
   const ConvProb* p;
   bool isA;
   int r0, rg, pg;          // first row (o or j) of this thread's micro-tile
-  u32x4 raw[2][VEC];       // A pooled: raw[S][0..NW) = window gradients; else the pixel vectors
-  uint64_t am[2][NW];      // A pooled: window argmaxes
-  int wkb, wn, wph, wpw;   // B pooled: (image, row, column) of this thread's first window of k-block wkb
-  // B generic: column r0 + q's tap offsets (du, dv) and element offset from
+  u32x4 raw[2][VEC];       // the pixel vectors
+  // B: column r0 + q's tap offsets (du, dv) and element offset from
   // the pixel's first channel (fixed per thread, so computed once); a column
   // past J gets a dv no pixel brings in range; bq: the bias column's q or -1
   int gdu[VEC], gdv[VEC], goff[VEC], bq;
@@ -962,8 +961,7 @@ struct WgradLoader {
     isA = __builtin_amdgcn_readfirstlane(threadIdx.x) < 128;  // waves 0-1: A, waves 2-3: B (wave-uniform)
     microtile_of(threadIdx.x % 128, rg, pg);
     r0 = (isA ? m0 : n0) + rg * VEC;
-    wkb = -1;
-    if constexpr (MODE == WG_GENERIC) {
+    {
       const int C = pr.C, KW = pr.KH, J = pr.KH * pr.KH * C;
       bq = J - r0 >= 0 && J - r0 < VEC ? J - r0 : -1;
 #pragma unroll
@@ -982,116 +980,10 @@ struct WgradLoader {
       }
     }
   }
-  // advance a pooled window position by `by` windows (row-major over images)
-  __device__ __forceinline__ void win_step(int& n, int& ph, int& pw, int by) const {
-    pw += by;
-    while (pw >= p->PW) {
-      pw -= p->PW;
-      if (++ph == p->PH) {
-        ph = 0;
-        ++n;
-      }
-    }
-  }
-  __device__ __forceinline__ int64_t out_rows() const {
-    return p->pool ? (int64_t)p->Nb * p->PH * p->PW : (int64_t)p->Nb * p->OH * p->OW;
-  }
   template <int S>
   __device__ __forceinline__ void load(int kb) {
-    if constexpr (MODE == WG_GENERIC) {
-      if (isA) loadA_generic<S>(kb);
-      else loadB_generic<S>(kb);
-    } else {
-      if (isA) loadA_fast<S>(kb);
-      else loadB_fast<S>(kb);
-    }
-  }
-  // A, whole-vector channels: a micro-tile is entirely below O or entirely past it
-  template <int S>
-  __device__ __forceinline__ void loadA_fast(int kb) {
-    const __amdgpu_buffer_rsrc_t rs = make_rsrc(p->G, out_rows() * p->O * (int64_t)sizeof(T));
-    const int O = p->O, o0 = r0, K = p->K;
-    const bool rows_in = o0 < O;
-    const int pix0 = kb * BK + pg * VEC;
-    if constexpr (POOL) {
-      const __amdgpu_buffer_rsrc_t rs_am = make_rsrc(p->gam, out_rows() * p->O);
-      // VEC consecutive pixels are NW whole windows; past the last pixel or
-      // channel: zero gradient and no argmax bit
-#pragma unroll
-      for (int wq = 0; wq < NW; ++wq) {
-        const int pix = pix0 + 4 * wq, idx = (pix >> 2) * O + o0;
-        const bool in = rows_in && pix < K;
-        raw[S][wq] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, in ? idx * (int)sizeof(T) : OOB, 0, 0));
-        am[S][wq] = in ? load_am_buf<T>(rs_am, idx) : 0ull;
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        const int pix = pix0 + e;
-        raw[S][e] = __builtin_bit_cast(
-            u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, rows_in && pix < K ? (pix * O + o0) * (int)sizeof(T) : OOB, 0, 0));
-      }
-    }
-  }
-  // B, whole-vector channels: a micro-tile's VEC columns are one tap's
-  // channels, or the bias chunk (1, 0, ..., 0), or past the bias column
-  template <int S>
-  __device__ __forceinline__ void loadB_fast(int kb) {
-    const __amdgpu_buffer_rsrc_t rs = make_rsrc(p->X, (int64_t)p->Nb * p->H * p->W * p->C * (int64_t)sizeof(T));
-    const int C = p->C, H = p->H, W = p->W, KW = p->KH, pad = p->pad, J = p->KH * p->KH * C, j0 = r0;
-    const bool bias_chunk = j0 == J, rows_in = j0 < J;
-    const int t = j0 / C, c0 = j0 - t * C, u = t / KW, vv = t - u * KW;
-    const int pix0 = kb * BK + pg * VEC;
-    if constexpr (POOL) {
-      // VEC consecutive pixels are NW whole windows; their positions are
-      // decoded once and then stepped (k-blocks arrive in order)
-      if (kb != wkb) {
-        const int w = pix0 >> 2, pp = p->PH * p->PW;
-        wn = w / pp;
-        const int rem = w - wn * pp;
-        wph = rem / p->PW;
-        wpw = rem - wph * p->PW;
-      }
-      int n = wn, ph = wph, pw = wpw;
-      win_step(wn, wph, wpw, BK / 4);
-      wkb = kb + 1;
-#pragma unroll
-      for (int wq = 0; wq < NW; ++wq) {
-        if (wq > 0) win_step(n, ph, pw, 1);
-        const int y0 = 2 * ph, x0 = 2 * pw;
-        const bool pin = pix0 + 4 * wq < p->K;
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          const int iy = y0 + (d >> 1) + u - pad, ix = x0 + (d & 1) + vv - pad;
-          const bool in = rows_in && pin && iy >= 0 && iy < H && ix >= 0 && ix < W;
-          u32x4 val = __builtin_bit_cast(
-              u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, in ? (((n * H + iy) * W + ix) * C + c0) * (int)sizeof(T) : OOB, 0, 0));
-          if (bias_chunk && pin) vset_bits<T>(val, 0, bits_of<T>(TT<T>::from_f(1.0f)));
-          raw[S][4 * wq + d] = val;
-        }
-      }
-    } else {
-      // decode the first pixel and step along x
-      int n, y, x;
-      decode_out_pixel(*p, pix0, n, y, x);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        const bool pin = pix0 + e < p->K;
-        const int iy = y + u - pad, ix = x + vv - pad;
-        const bool in = rows_in && pin && iy >= 0 && iy < H && ix >= 0 && ix < W;
-        u32x4 val = __builtin_bit_cast(
-            u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, in ? (((n * H + iy) * W + ix) * C + c0) * (int)sizeof(T) : OOB, 0, 0));
-        if (bias_chunk && pin) vset_bits<T>(val, 0, bits_of<T>(TT<T>::from_f(1.0f)));
-        raw[S][e] = val;
-        if (++x == p->OW) {
-          x = 0;
-          if (++y == p->OH) {
-            y = 0;
-            ++n;
-          }
-        }
-      }
-    }
+    if (isA) loadA_generic<S>(kb);
+    else loadB_generic<S>(kb);
   }
   // A, any channel count, pooled or not: final pixel vectors, element by element
   template <int S>
@@ -1165,22 +1057,8 @@ struct WgradLoader {
   // stage: A tile at stage[0], B tile at stage[BM * LDK]
   template <int S>
   __device__ __forceinline__ void store(T* stage) {
-    u32x4 pixv[VEC], out[VEC];
-    if (POOL && isA) {
-      // each window's gradient lands on its argmax pixel only
-#pragma unroll
-      for (int wq = 0; wq < NW; ++wq)
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          u32x4 v = raw[S][wq];
-          select_am<T>(v, am[S][wq], d);
-          pixv[4 * wq + d] = v;
-        }
-    } else {
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) pixv[e] = raw[S][e];
-    }
-    transpose_block<T>(pixv, out);
+    u32x4 out[VEC];
+    transpose_block<T>(raw[S], out);
     T* sm = isA ? stage : stage + BM * LDK;
     const int rl = rg * VEC;
 #pragma unroll
@@ -2706,7 +2584,7 @@ void conv_halo_kernel(const ConvProb* __restrict__ probs, const int32_t* __restr
   }
 }
 
-template <typename T, int BM, int BN, int BK, int MODE>
+template <typename T, int BM, int BN, int BK>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_wgrad_kernel(const ConvProb* __restrict__ probs,
                                                          const int32_t* __restrict__ tile_map, int64_t wsoff) {
   using TL = Tile<T, BM, BN, BK>;
@@ -2727,7 +2605,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
 #pragma unroll
     for (int j = 0; j < TL::FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  WgradLoader<T, BM, BN, BK, MODE> ld;
+  WgradLoader<T, BM, BN, BK> ld;
   ld.init(p, m0, n0);
   const int nkb = (p.K + BK - 1) / BK;
   const int kb0 = split * p.kchunk, kb1 = min(nkb, kb0 + p.kchunk);
@@ -2753,11 +2631,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
 }
 
 // ---------------------------------------------------------------------------
-// bf16 conv weight gradient on the grouped GEMM's machinery: 16 waves of
-// 32x32x16 MFMA tiles, loads two k-blocks ahead, and both operands staged in
-// LDS k-major - as they lie in memory, [pixel][channel] - and turned into MFMA
-// operands by the LDS transpose reads. For blocks whose channel counts O and
-// C are whole 16-byte vectors (pooled or not).
+// Conv weight gradient on the grouped GEMM's machinery (bf16: waves of 32x32x16
+// MFMA tiles; fp32: 16x16x4): loads two k-blocks ahead, and both operands
+// staged in LDS k-major - as they lie in memory, [pixel][channel] - and turned
+// into MFMA operands by the LDS transpose reads (fp32: read element-wise). For
+// blocks whose channel counts O and C are whole 16-byte vectors (pooled or not).
 //   A (rows o):      dZ[pixel][o], gathered from the pooled gradient G[w][o]
 //                    and the window argmax (pooled), or G[pixel][o] itself;
 //   B (rows j):      the input patch X[n][y+u-pad][x+v-pad][c], j = (u,v,c),
@@ -2770,9 +2648,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
 // coordinates as counters stepped once per k-block (uniform steps, carries by
 // compare and subtract), with no per-block division or 32-bit multiply (both
 // quarter-rate). Offsets are 32-bit: every conv tensor is under 2^31 bytes.
-template <int ROWS, int BK, int NT, int SLOTS, int PAD, bool POOL>
+template <typename T, int ROWS, int BK, int NT, int SLOTS, int PAD, bool POOL>
 struct ConvKA {
-  static constexpr int VEC = 8, CPR = ROWS / VEC, LDR = ROWS + PAD, NV = BK * CPR / NT;
+  static constexpr int VEC = TT<T>::VEC, ES = sizeof(T), CPR = ROWS / VEC, LDR = ROWS + PAD, NV = BK * CPR / NT;
   static_assert(NV >= 1 && BK * CPR == NV * NT, "whole chunks per thread and k-block");
   static_assert(BK % 4 == 0 && (NT / CPR) % 4 == 0, "k-blocks hold whole windows; a thread's chunks share one window position");
   __amdgpu_buffer_rsrc_t rs, rs_am;
@@ -2785,20 +2663,20 @@ struct ConvKA {
   // o >= O are read without a range test: they feed accumulator rows that
   // are never stored. Pixels past the last one lie past both buffers' ranges
   // and read zero.
-  __device__ __forceinline__ void init(const ConvProb& p, int o0, int kb0) {
+  __device__ __forceinline__ void init(const ConvProb& p, int o0, int pix0) {
     const int k = threadIdx.x / CPR, o = o0 + (threadIdx.x % CPR) * VEC;
-    const int pix = kb0 * BK + k;
+    const int pix = pix0 + k;
     const uint32_t e = (uint32_t)((POOL ? pix >> 2 : pix) * p.O + o);  // element offset of chunk 0 in G
     const uint32_t step = (uint32_t)((POOL ? BK / 4 : BK) * p.O), s1 = (uint32_t)((POOL ? NT / CPR / 4 : NT / CPR) * p.O);
-    offb = 2 * e;
+    offb = ES * e;
     offa = e;
-    stepb = 2 * step;
+    stepb = ES * step;
     stepa = step;
-    sb1 = 2 * s1;
+    sb1 = ES * s1;
     sa1 = s1;
-    sm_off = kmaj_bf16<LDR>(k, (threadIdx.x % CPR) * VEC);
+    sm_off = kmaj_off<T, LDR>(k, (threadIdx.x % CPR) * VEC);
     const int64_t rows = POOL ? (int64_t)p.Nb * p.PH * p.PW : (int64_t)p.Nb * p.OH * p.OW;
-    rs = make_rsrc(p.G, rows * p.O * (int64_t)sizeof(bf16_t));
+    rs = make_rsrc(p.G, rows * p.O * (int64_t)ES);
     if constexpr (POOL) rs_am = make_rsrc(p.gam, rows * p.O);
   }
   // the next k-block (the loop issues blocks in order, one call each)
@@ -2807,17 +2685,17 @@ struct ConvKA {
 #pragma unroll
     for (int s = 0; s < NV; ++s) {
       r[S][s] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, offb + s * sb1, 0, 0));
-      if constexpr (POOL) am[S][s] = load_am_buf<bf16_t>(rs_am, offa + s * sa1);
+      if constexpr (POOL) am[S][s] = load_am_buf<T>(rs_am, offa + s * sa1);
     }
     offb += stepb;
     offa += stepa;
   }
   template <int S>
-  __device__ __forceinline__ void store(bf16_t* sm) const {
+  __device__ __forceinline__ void store(T* sm) const {
 #pragma unroll
     for (int s = 0; s < NV; ++s) {
       u32x4 v = r[S][s];
-      if constexpr (POOL) select_am<bf16_t>(v, am[S][s], (threadIdx.x / CPR) & 3);
+      if constexpr (POOL) select_am<T>(v, am[S][s], (threadIdx.x / CPR) & 3);
       *(u32x4*)(sm + sm_off + (s * (NT / CPR)) * LDR) = v;
     }
   }
@@ -2836,9 +2714,9 @@ struct ConvKA {
 // same rows and the wrap to the next image is the same for all: a lane keeps
 // its input row and byte offset, stepped by wave-uniform amounts. Otherwise a
 // lane keeps (a, b) and the element offset q and wraps them itself.
-template <int ROWS, int BK, int NT, int SLOTS, int PAD, bool POOL, bool UNI>
+template <typename T, int ROWS, int BK, int NT, int SLOTS, int PAD, bool POOL, bool UNI>
 struct ConvKB {
-  static constexpr int VEC = 8, CPR = ROWS / VEC, LDR = ROWS + PAD, NV = BK * CPR / NT, F = POOL ? 2 : 1;
+  static constexpr int VEC = TT<T>::VEC, ES = sizeof(T), CPR = ROWS / VEC, LDR = ROWS + PAD, NV = BK * CPR / NT, F = POOL ? 2 : 1;
   static constexpr int ST = POOL ? BK / 4 : BK;  // windows (or pixels) per k-block
   static constexpr uint32_t OOB = 0x7ffffff0u;   // a byte offset past every range: the load returns zero
   static_assert(NV >= 1 && BK * CPR == NV * NT, "whole chunks per thread and k-block");
@@ -2862,11 +2740,11 @@ struct ConvKB {
   uint32_t qb[NV];
   bool xin[NV];
   u32x4 r[SLOTS][NV];
-  __device__ __forceinline__ void init(const ConvProb& pr, int j0, int kb0) {
+  __device__ __forceinline__ void init(const ConvProb& pr, int j0, int pix0) {
     const int k = threadIdx.x / CPR;
     const int j = j0 + (threadIdx.x % CPR) * VEC, J = pr.KH * pr.KH * pr.C;
     jin = j < J;
-    orm = j == J ? bits_of<bf16_t>(TT<bf16_t>::from_f(1.0f)) : 0u;
+    orm = j == J ? bits_of<T>(TT<T>::from_f(1.0f)) : 0u;
     const int tap = j / pr.C, c0 = j - tap * pr.C, u = tap / pr.KH, v = tap - u * pr.KH;
     H = pr.H;
     W = pr.W;
@@ -2875,22 +2753,22 @@ struct ConvKB {
     const int d = POOL ? (k & 3) : 0, dy = d >> 1, dx = d & 1;
     ey = dy + u - pr.pad;  // input row of the chunk's pixel: F * a + ey
     ex = dx + v - pr.pad;
-    sm_off = kmaj_bf16<LDR>(k, (threadIdx.x % CPR) * VEC);
+    sm_off = kmaj_off<T, LDR>(k, (threadIdx.x % CPR) * VEC);
     const int plane = A * B;
     if constexpr (UNI) {
-      const int C2 = 2 * pr.C;
+      const int CB = ES * pr.C;
       if (ST % plane == 0) {  // whole images per block
         ra = 0;
         dyn = dyw = 0;
-        dqn = dqw = (uint32_t)((ST / plane) * H * W * C2);
+        dqn = dqw = (uint32_t)((ST / plane) * H * W * CB);
       } else {  // whole rows of one image per block
         ra = ST / B;
         dyn = F * ra;
         dyw = F * ra - F * A;
-        dqn = (uint32_t)(F * ra * W * C2);
-        dqw = (uint32_t)((F * ra * W + H * W - F * A * W) * C2);
+        dqn = (uint32_t)(F * ra * W * CB);
+        dqw = (uint32_t)((F * ra * W + H * W - F * A * W) * CB);
       }
-      ablk = ((kb0 * ST) % plane) / B;
+      ablk = ((POOL ? pix0 >> 2 : pix0) % plane) / B;
     } else {
       // the step of BK pixels (BK / 4 windows) in (n, a, b) and its offsets
       const int sn = ST / plane, rem = ST - sn * plane;
@@ -2902,7 +2780,7 @@ struct ConvKB {
     }
 #pragma unroll
     for (int s = 0; s < NV; ++s) {
-      const int pix = kb0 * BK + k + s * (NT / CPR), m = POOL ? pix >> 2 : pix;
+      const int pix = pix0 + k + s * (NT / CPR), m = POOL ? pix >> 2 : pix;
       const int n = m / plane, r2 = m - n * plane;
       const int aa = r2 / B, bb = r2 - aa * B;
       if constexpr (UNI) {
@@ -2910,14 +2788,14 @@ struct ConvKB {
         const int ix = F * bb + ex;
         xin[s] = jin && (unsigned)ix < (unsigned)W;
         // modulo 2^32: exact again once the row is inside the image
-        qb[s] = 2u * (uint32_t)(((n * H + iy[s]) * W + ix) * pr.C + c0);
+        qb[s] = (uint32_t)ES * (uint32_t)(((n * H + iy[s]) * W + ix) * pr.C + c0);
       } else {
         a[s] = aa;
         b[s] = bb;
         q[s] = ((n * H + F * aa + ey) * W + F * bb + ex) * pr.C + c0;
       }
     }
-    rs = make_rsrc(pr.X, (int64_t)pr.Nb * pr.H * pr.W * pr.C * (int64_t)sizeof(bf16_t));
+    rs = make_rsrc(pr.X, (int64_t)pr.Nb * pr.H * pr.W * pr.C * (int64_t)ES);
   }
   // the next k-block (the loop issues blocks in order, one call each)
   template <int S>
@@ -2946,7 +2824,7 @@ struct ConvKB {
         const int iyy = F * a[s] + ey, ix = F * b[s] + ex;
         const bool in = jin && (unsigned)iyy < (unsigned)H && (unsigned)ix < (unsigned)W;
         u32x4 val = __builtin_bit_cast(
-            u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, in ? (uint32_t)q[s] * 2u : OOB, 0, 0));
+            u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, in ? (uint32_t)q[s] * (uint32_t)ES : OOB, 0, 0));
         val[0] |= orm;
         r[S][s] = val;
         q[s] += q0;
@@ -2962,25 +2840,35 @@ struct ConvKB {
     }
   }
   template <int S>
-  __device__ __forceinline__ void store(bf16_t* sm) const {
+  __device__ __forceinline__ void store(T* sm) const {
 #pragma unroll
     for (int s = 0; s < NV; ++s) *(u32x4*)(sm + sm_off + (s * (NT / CPR)) * LDR) = r[S][s];
   }
 };
 
-// NARROW: tiles of CONV_WG_NARROW_BM output channels (8 waves), for launches
-// whose blocks have at most that many; else 128 rows (16 waves).
-template <bool POOL, bool NARROW>
-__global__ __launch_bounds__((NARROW ? 512 : 1024)) __attribute__((amdgpu_waves_per_eu((NARROW ? 4 : 8))))
+// Tiles of BM output channels, the smallest that every block of the launch fits
+// (bf16 64 or 128, 8 or 16 waves; fp32 16, 32 or 64, 4 waves: an fp32 tile is
+// bound by its MFMAs, so the rows past O cost most there). The 16-row tile takes
+// 64-pixel k-blocks, which its chunks per thread divide. fp32 against 64-row
+// tiles with both operands transposed in registers: 4 LeNets (8-16 channels)
+// 35 and 59 -> 12 and 26 us per launch, step 216 -> 160 us; 4 CNNs of 16-40
+// channels 36 and 36 -> 18 and 19 us, step 158 -> 124.
+template <typename T, int BM> struct WgShape {
+  static constexpr bool B16 = sizeof(T) == 2;
+  static constexpr int BN = B16 ? CONV_BN_BF16 : CONV_BN_F32, BK = B16 ? CONV_BK_BF16 : BM == 16 ? 64 : CONV_BK_F32;
+  static constexpr int WGM = B16 ? BM / 32 : BM == 16 ? 1 : 2, WGN = B16 ? 4 : 4 / WGM;  // bf16: 32x32 wave tiles
+  using MM = GemmMma<T, BM, BN, BK, WGM, WGN>;
+  static constexpr int WPE = B16 ? MM::NT / 128 : 4;
+};
+template <typename T, bool POOL, int BM>
+__global__ __launch_bounds__((WgShape<T, BM>::MM::NT)) __attribute__((amdgpu_waves_per_eu((WgShape<T, BM>::WPE))))
 void conv_wgrad_mfma_kernel(const ConvProb* __restrict__ probs, const int32_t* __restrict__ tile_map,
                             int64_t wsoff) {
-  constexpr int BM = NARROW ? CONV_WG_NARROW_BM : CONV_BM_BF16, BN = CONV_BN_BF16, BK = CONV_BK_BF16;
-  using MM = GemmMma<bf16_t, BM, BN, BK, NARROW ? 2 : 4, 4>;  // 32x32 wave tiles
-  static_assert(MM::NT == (NARROW ? 512 : 1024), "launch bounds");
-  constexpr int NT = MM::NT, D = UN_GEMM_DEPTH;
-  static_assert(MM::LDR_A * BK <= Tile<bf16_t, BM, BN, BK>::A_ELEMS &&
-                    MM::LDR_B * BK <= Tile<bf16_t, BM, BN, BK>::B_ELEMS, "k-major stages fit the stage buffers");
-  __shared__ __attribute__((aligned(16))) char smem[Smem<bf16_t, BM, BN, BK>::BYTES];
+  using WS = WgShape<T, BM>;
+  using MM = typename WS::MM;
+  constexpr int BN = WS::BN, BK = WS::BK, KB = WS::B16 ? CONV_BK_BF16 : CONV_BK_F32;
+  constexpr int NT = MM::NT, D = UN_GEMM_DEPTH, PAD = WS::B16 ? KMAJ_PAD_BF16 : KMAJ_PAD_F32;
+  __shared__ __attribute__((aligned(16))) char smem[2 * (MM::A_ELEMS + MM::B_ELEMS) * sizeof(T)];
   const int prob = tile_map[2 * blockIdx.x];
   int local = tile_map[2 * blockIdx.x + 1];
   if (prob < 0) return;  // padding of the XCD-ordered tile list
@@ -2990,21 +2878,23 @@ void conv_wgrad_mfma_kernel(const ConvProb* __restrict__ probs, const int32_t* _
   local -= split * per_split;
   const int tm = local / p.tiles_n, tn = local - tm * p.tiles_n;
   const int m0 = tm * BM, n0 = tn * BN;
-  const int kb0 = split * p.kchunk, nkb = min((p.K + BK - 1) / BK, kb0 + p.kchunk) - kb0;
+  // pixels [pix0, pix0 + kchunk k-blocks of KB), whole k-blocks of BK (the
+  // planner's chunks are multiples of it)
+  const int pix0 = split * p.kchunk * KB, nkb = (min(p.K - pix0, p.kchunk * KB) + BK - 1) / BK;
 
   typename MM::Acc acc;
   MM::zero(acc);
-  ConvKA<BM, BK, NT, D, KMAJ_PAD_BF16, POOL> la;
-  la.init(p, m0, kb0);
-  using KBU = ConvKB<BN, BK, NT, D, KMAJ_PAD_BF16, POOL, true>;
+  ConvKA<T, BM, BK, NT, D, PAD, POOL> la;
+  la.init(p, m0, pix0);
+  using KBU = ConvKB<T, BN, BK, NT, D, PAD, POOL, true>;
   if (KBU::uniform(p)) {
     KBU lb;
-    lb.init(p, n0, kb0);
-    gemm_loop<bf16_t, BM, BN, BK, D, MM, OP_KMAJ, OP_KMAJ>(la, lb, nkb, (bf16_t*)smem, acc);
+    lb.init(p, n0, pix0);
+    gemm_loop<T, BM, BN, BK, D, MM, OP_KMAJ, OP_KMAJ>(la, lb, nkb, (T*)smem, acc);
   } else {
-    ConvKB<BN, BK, NT, D, KMAJ_PAD_BF16, POOL, false> lb;
-    lb.init(p, n0, kb0);
-    gemm_loop<bf16_t, BM, BN, BK, D, MM, OP_KMAJ, OP_KMAJ>(la, lb, nkb, (bf16_t*)smem, acc);
+    ConvKB<T, BN, BK, NT, D, PAD, POOL, false> lb;
+    lb.init(p, n0, pix0);
+    gemm_loop<T, BM, BN, BK, D, MM, OP_KMAJ, OP_KMAJ>(la, lb, nkb, (T*)smem, acc);
   }
 
   // this split's partial sums to ws[split][o][j] (32-bit offsets within the
@@ -3786,30 +3676,31 @@ hipError_t launch_conv_halo(bool bf16, bool dgrad, const ConvProb* probs, const 
   return hipGetLastError();
 }
 
-hipError_t launch_conv_wgrad(bool bf16, int mode, const ConvProb* probs, const int32_t* tile_map, int ntiles,
+hipError_t launch_conv_wgrad(bool bf16, int mode, int bm, const ConvProb* probs, const int32_t* tile_map, int ntiles,
                              int64_t wsoff, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-#define UN_WGRAD_LAUNCH(T, BM, BN, BK, M) \
-  hipLaunchKernelGGL((conv_wgrad_kernel<T, BM, BN, BK, M>), dim3(ntiles), dim3(256), 0, s, probs, tile_map, wsoff)
-  if (bf16) {
-    constexpr int NT = GemmMma<bf16_t, CONV_BM_BF16, CONV_BN_BF16, CONV_BK_BF16, 4, 4>::NT;
-    const bool narrow = (mode & WG_NARROW) != 0;
-    mode &= ~WG_NARROW;
-    if (mode == WG_POOLED && narrow)
-      hipLaunchKernelGGL((conv_wgrad_mfma_kernel<true, true>), dim3(ntiles), dim3(NT / 2), 0, s, probs, tile_map, wsoff);
-    else if (mode == WG_POOLED)
-      hipLaunchKernelGGL((conv_wgrad_mfma_kernel<true, false>), dim3(ntiles), dim3(NT), 0, s, probs, tile_map, wsoff);
-    else if (mode == WG_PLAIN && narrow)
-      hipLaunchKernelGGL((conv_wgrad_mfma_kernel<false, true>), dim3(ntiles), dim3(NT / 2), 0, s, probs, tile_map, wsoff);
-    else if (mode == WG_PLAIN)
-      hipLaunchKernelGGL((conv_wgrad_mfma_kernel<false, false>), dim3(ntiles), dim3(NT), 0, s, probs, tile_map, wsoff);
-    else UN_WGRAD_LAUNCH(bf16_t, CONV_BM_BF16, CONV_BN_BF16, CONV_BK_BF16, WG_GENERIC);
-  } else {
-    if (mode == WG_POOLED) UN_WGRAD_LAUNCH(float, CONV_BM_F32, CONV_BN_F32, CONV_BK_F32, WG_POOLED);
-    else if (mode == WG_PLAIN) UN_WGRAD_LAUNCH(float, CONV_BM_F32, CONV_BN_F32, CONV_BK_F32, WG_PLAIN);
-    else UN_WGRAD_LAUNCH(float, CONV_BM_F32, CONV_BN_F32, CONV_BK_F32, WG_GENERIC);
+  if (mode == WG_GENERIC) {
+    if (bf16)
+      hipLaunchKernelGGL((conv_wgrad_kernel<bf16_t, CONV_BM_BF16, CONV_BN_BF16, CONV_BK_BF16>), dim3(ntiles), dim3(256),
+                         0, s, probs, tile_map, wsoff);
+    else
+      hipLaunchKernelGGL((conv_wgrad_kernel<float, CONV_BM_F32, CONV_BN_F32, CONV_BK_F32>), dim3(ntiles), dim3(256), 0,
+                         s, probs, tile_map, wsoff);
+    return hipGetLastError();
   }
-#undef UN_WGRAD_LAUNCH
+  auto go = [&](auto t, auto rows) {
+    using T = decltype(t);
+    constexpr int BM = decltype(rows)::value, NT = WgShape<T, BM>::MM::NT;
+    if (mode == WG_POOLED)
+      hipLaunchKernelGGL((conv_wgrad_mfma_kernel<T, true, BM>), dim3(ntiles), dim3(NT), 0, s, probs, tile_map, wsoff);
+    else
+      hipLaunchKernelGGL((conv_wgrad_mfma_kernel<T, false, BM>), dim3(ntiles), dim3(NT), 0, s, probs, tile_map, wsoff);
+  };
+  if (bf16 && bm == 64) go(bf16_t{}, std::integral_constant<int, 64>{});
+  else if (bf16) go(bf16_t{}, std::integral_constant<int, 128>{});
+  else if (bm == 16) go(float{}, std::integral_constant<int, 16>{});
+  else if (bm == 32) go(float{}, std::integral_constant<int, 32>{});
+  else go(float{}, std::integral_constant<int, 64>{});
   return hipGetLastError();
 }
 

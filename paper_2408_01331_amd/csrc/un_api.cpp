@@ -139,6 +139,7 @@ struct Launch {
   int count;
   int mode = 0;       // GEMM: tile variant; conv weight gradient: code variant (launch_conv_wgrad); CE: problems needing the row pass
   size_t lds = 0;     // halo conv: dynamic LDS bytes
+  int bm = 0;         // conv weight gradient: output channels per tile
 };
 
 struct EventRec {
@@ -970,14 +971,16 @@ static void build_tables(un_ctx* c, Tables& T) {
         by[!whole ? 0 : p.pool ? 1 : 2].push_back(p);
       }
       for (int m = 0; m < 3; ++m) {
-        // bf16 whole-vector blocks that all have few output channels: 64-row tiles
-        bool narrow = bf && m != 0 && !by[m].empty();
-        for (auto& p : by[m]) narrow = narrow && p.O <= CONV_WG_NARROW_BM;
-        if (narrow)
-          for (auto& p : by[m]) p.bm = CONV_WG_NARROW_BM;
+        int bm = 0;  // whole-vector blocks: rows of their tiles
+        if (m != 0)
+          for (auto& p : by[m]) bm = std::max(bm, conv_wg_rows(bf, p.O));
+        for (auto& p : by[m]) p.bm = bm;
         const size_t before = out.size();
         emit_conv_one(by[m], out, kind, kclass);
-        if (out.size() > before) out.back().mode = m | (narrow ? WG_NARROW_BIT : 0);
+        if (out.size() > before) {
+          out.back().mode = m;
+          out.back().bm = bm;
+        }
       }
     }
   };
@@ -1706,6 +1709,10 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
           return cdiv(nkb, kchunk);
         };
         b.splits = cut(b.O, b.C, b.kchunk);
+        if (!bf && conv_wg_rows(bf, b.O) == 16) {  // its tiles take two k-blocks at once
+          b.kchunk = (int)rup(b.kchunk, 2);
+          b.splits = cdiv(nkb, b.kchunk);
+        }
         b.ldws = rup(J + 1, 4);
         b.ws_size = (size_t)b.splits * b.O * b.ldws * 4;  // placed in the workspace range below
         // un_step_scratch's limit counts the model's own channels
@@ -1949,7 +1956,7 @@ static hipError_t run_launch(un_ctx* c, const Launch& l, float lr) {
       e = launch_conv_dgrad(c->bf16, c->at<ConvProb>(l.probs), c->at<int32_t>(l.map), l.count, c->stream);
       break;
     case 3:
-      e = launch_conv_wgrad(c->bf16, l.mode, c->at<ConvProb>(l.probs), c->at<int32_t>(l.map), l.count, c->wsoff,
+      e = launch_conv_wgrad(c->bf16, l.mode, l.bm, c->at<ConvProb>(l.probs), c->at<int32_t>(l.map), l.count, c->wsoff,
                             c->stream);
       break;
     case 7:
