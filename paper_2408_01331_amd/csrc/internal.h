@@ -158,6 +158,7 @@ struct ReduceProb {
   const float* ws;
   int64_t ldws;
   int32_t splits, O, J, C;    // J = KH*KW*C weight columns (+1 bias column in ws)
+  int32_t rows;               // output rows per thread: VEC (O a multiple of it, 16-byte aligned WT) or 1
   int32_t blk_base;
   int32_t model;
   float* gW;
