@@ -307,7 +307,8 @@ hipError_t launch_conv_wgrad(bool bf16, int mode, int bm, const ConvProb* probs,
                              int64_t wsoff, hipStream_t s);
 // Halo-tiled forward (dgrad = false) or data gradient (dgrad = true); every
 // problem of the launch has halo != 0 (either tile shape).
-hipError_t launch_conv_halo(bool bf16, bool dgrad, const ConvProb* probs, const int32_t* tile_map, int ntiles,
+// small: every problem has a small tile shape, else none.
+hipError_t launch_conv_halo(bool bf16, bool dgrad, bool small, const ConvProb* probs, const int32_t* tile_map, int ntiles,
                             size_t lds_bytes, hipStream_t s);
 hipError_t launch_reduce(bool bf16, const ReduceProb* probs, const int32_t* blk_prob, int nblocks, float lr,
                          const float* lrv, const OptHp* opt, bool keep_grads, int64_t wsoff, hipStream_t s);

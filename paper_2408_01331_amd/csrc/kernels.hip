@@ -2392,7 +2392,7 @@ struct HaloSmem {
 // same n-column. Those reuse the tap tables and row bases, and (at most two
 // k-blocks) the weights in LDS; their rows are fetched into registers before
 // the previous tile's epilogue.
-template <typename T, int BM, int BN, int BK, bool DGRAD, int NW>
+template <typename T, int BM, int BN, int BK, bool DGRAD, int NW, bool SMALL = false>
 __device__ __forceinline__ void halo_tile(const ConvProb& p, int local, char* smem) {
   using TL = Tile<T, BM, BN, BK, NW>;
   using L = std::conditional_t<sizeof(T) == 2, Acc32<BM, BN, NW>, Acc16<T, BM, BN, BK, NW>>;
@@ -2400,7 +2400,7 @@ __device__ __forceinline__ void halo_tile(const ConvProb& p, int local, char* sm
   using HS = HaloSmem<T, BN, BK>;
   constexpr int VEC = TT<T>::VEC, CPB = BK / VEC;
   static_assert(TL::B_ELEMS == HS::B_ELEMS, "halo LDS budget assumes one pad chunk per row");
-  static_assert(NT == (sizeof(T) == 2 ? HALO_NT_BF16 : HALO_NT_F32), "halo workgroup size");
+  static_assert(SMALL || NT == (sizeof(T) == 2 ? HALO_NT_BF16 : HALO_NT_F32), "halo workgroup size");
   T* sB = (T*)smem;
   int* qa = (int*)(sB + 2 * TL::B_ELEMS);
   int* qb = qa + HALO_QMAX;
@@ -2412,7 +2412,7 @@ __device__ __forceinline__ void halo_tile(const ConvProb& p, int local, char* sm
   const int SH = DGRAD ? p.H : wo ? 2 * p.PH : p.OH, SW = DGRAD ? p.W : wo ? 2 * p.PW : p.OW;
   // (not the tall tiles: their accumulators leave no registers for the
   // fetched rows across the epilogue; the host plans none)
-  constexpr bool MULTI = !DGRAD && BM <= 2 * (sizeof(T) == 2 ? CONV_BM_BF16 : CONV_BM_F32);
+  constexpr bool MULTI = !SMALL && !DGRAD && BM <= 2 * (sizeof(T) == 2 ? CONV_BM_BF16 : CONV_BM_F32);
   const int mt = MULTI ? max(1, min(p.mt, p.tiles_m - tm0)) : 1;
   // first operand image and row of the m-tile (wave-uniform; an image has tpi
   // row tiles, or a tile has imgs images)
@@ -2581,6 +2581,25 @@ void conv_halo_kernel(const ConvProb* __restrict__ probs, const int32_t* __restr
     halo_tile<T, 2 * BM, BN / 2, BK, DGRAD, NW>(p, local, smem);
   } else {
     if constexpr (!DGRAD && sizeof(T) == 2) halo_tile<T, 4 * BM, BN / 2, BK, DGRAD, NW>(p, local, smem);
+  }
+}
+
+// Halo-tiled pass of a launch whose tiles leave CUs idle (HALO_SMALL_MAX): small
+// tiles of four waves, bf16 64x64 or 128x32, fp32 32x32 or 64x16. The order of k is that
+// of the other shapes, so results do not depend on the choice.
+template <typename T, bool DGRAD>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+void conv_halo_small_kernel(const ConvProb* __restrict__ probs, const int32_t* __restrict__ tile_map) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int prob = tile_map[2 * blockIdx.x], local = tile_map[2 * blockIdx.x + 1];
+  if (prob < 0) return;
+  const ConvProb& p = probs[prob];
+  if constexpr (sizeof(T) == 4) {
+    if (p.bn == 32) halo_tile<T, 32, 32, CONV_BK_F32, DGRAD, 4, true>(p, local, smem);
+    else halo_tile<T, 64, 16, CONV_BK_F32, DGRAD, 4, true>(p, local, smem);
+  } else {
+    if (p.bn == 64) halo_tile<T, 64, 64, CONV_BK_BF16, DGRAD, 4, true>(p, local, smem);
+    else halo_tile<T, 128, 32, CONV_BK_BF16, DGRAD, 4, true>(p, local, smem);
   }
 }
 
@@ -3670,7 +3689,7 @@ hipError_t launch_conv_dgrad(bool bf16, const ConvProb* probs, const int32_t* ti
   return hipGetLastError();
 }
 
-hipError_t launch_conv_halo(bool bf16, bool dgrad, const ConvProb* probs, const int32_t* tile_map, int ntiles,
+hipError_t launch_conv_halo(bool bf16, bool dgrad, bool small, const ConvProb* probs, const int32_t* tile_map, int ntiles,
                             size_t lds_bytes, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   // allow dynamic LDS up to the halo budget (above the default cap)
@@ -3688,9 +3707,25 @@ hipError_t launch_conv_halo(bool bf16, bool dgrad, const ConvProb* probs, const 
     r = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_halo_kernel<float, CONV_BM_F32, CONV_BN_F32, CONV_BK_F32, false>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, HALO_LDS_F32);
     if (r != hipSuccess) e = r;
+    const void* small_k[4] = {reinterpret_cast<const void*>(&conv_halo_small_kernel<bf16_t, false>),
+                              reinterpret_cast<const void*>(&conv_halo_small_kernel<bf16_t, true>),
+                              reinterpret_cast<const void*>(&conv_halo_small_kernel<float, false>),
+                              reinterpret_cast<const void*>(&conv_halo_small_kernel<float, true>)};
+    for (int k = 0; k < 4; ++k) {
+      r = hipFuncSetAttribute(small_k[k], hipFuncAttributeMaxDynamicSharedMemorySize, k < 2 ? HALO_LDS_BF16 : HALO_LDS_F32);
+      if (r != hipSuccess) e = r;
+    }
     return e;
   }();
   if (attr != hipSuccess) return attr;
+  if (small) {
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(ntiles), dim3(256), lds_bytes, s, probs, tile_map); };
+    if (bf16 && dgrad) go(conv_halo_small_kernel<bf16_t, true>);
+    else if (bf16) go(conv_halo_small_kernel<bf16_t, false>);
+    else if (dgrad) go(conv_halo_small_kernel<float, true>);
+    else go(conv_halo_small_kernel<float, false>);
+    return hipGetLastError();
+  }
   if (bf16) {
     constexpr int NT = 64 * halo_waves<bf16_t>();
     if (dgrad)

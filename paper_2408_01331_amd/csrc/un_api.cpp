@@ -40,6 +40,16 @@ using namespace un;
 
 namespace {
 
+// A halo conv launch of at most this many tiles runs small ones: four per CU
+// in place of two, with a quarter of the rows to stage and of the k loop to wait
+// for each. Steps without / with small tiles up to 256 / 512 / 1024 / 1536
+// tiles, in us: resnet8 358 / 338 / 325 / 326 / 326; 7 bf16 models on 3
+// datasets 181 / 170 / 168 / 167 / 167; 11 bf16 CNNs on 28 x 28 118 / 115 / 110
+// / 109 / 102; cifar16's smallest launch has 1664 (with it small 1189 instead of
+// 1143). fp32 tiles are bound by their MFMAs sooner: 4 LeNets 161 / 156 / 158 /
+// 158 / 167, the 7 models 167 / 154 / 155 / 157 / 157.
+constexpr int HALO_SMALL_MAX = 1536, HALO_SMALL_MAX_F32 = 256;
+
 // A GEMM launch of at most this many large tiles (one per CU) runs small ones:
 // the launch then lasts as long as one tile's chain of k-blocks, and a small
 // tile's k-block reads a quarter of the LDS bytes and (fp32) runs a quarter of
@@ -715,6 +725,12 @@ static bool try_halo(ConvProb& p, bool bf, bool dgrad, int BM, int BN) {
   return true;
 }
 
+// The same with the small tile shapes.
+static bool try_halo_small(ConvProb& p, bool bf, bool dgrad) {
+  const int u = bf ? 32 : 16;  // the narrower shape takes passes of at most u columns
+  return p.N > u ? try_halo(p, bf, dgrad, 2 * u, 2 * u) : try_halo(p, bf, dgrad, 4 * u, u);
+}
+
 // A halo forward problem that a multi-tile workgroup can run: one channel
 // block, wide or narrow tiles (a tall tile's accumulators leave no registers
 // for the rows fetched ahead), staged rows within the fetch-ahead registers.
@@ -739,6 +755,27 @@ static void plan_halo(ConvProb& p, bool bf, bool dgrad) {
 // ==========================================================================
 // Descriptor tables of one step (the models in c->active only)
 // ==========================================================================
+static ConvProb conv_geometry(const Block& b, int batch) {
+  ConvProb p{};
+  p.Nb = batch;
+  p.C = b.C;
+  p.H = b.H;
+  p.W = b.W;
+  p.O = b.O;
+  p.KH = b.KH;
+  p.pad = b.pad;
+  p.OH = b.OH;
+  p.OW = b.OW;
+  p.PH = b.PH;
+  p.PW = b.PW;
+  p.pool = b.pool;
+  p.relu = b.relu;
+  p.prev_relu = b.prev_relu;
+  p.splits = 1;
+  p.mt = 1;
+  return p;
+}
+
 struct Tables {
   std::vector<char> host;    // tables as uploaded (pointers encoded as arena offset + 1)
   std::vector<size_t> fix;   // byte offsets of the encoded pointer fields
@@ -898,7 +935,7 @@ static void build_tables(un_ctx* c, Tables& T) {
     size_t mo = put(map.data(), map.size() * 4);
     out.push_back(Launch{0, kclass, po, mo, (int)(map.size() / 2), variant});
   };
-  auto emit_conv_one = [&](std::vector<ConvProb>& ps, std::vector<Launch>& out, int kind, int kclass) {
+  auto emit_conv_one = [&](std::vector<ConvProb>& ps, std::vector<Launch>& out, int kind, int kclass, bool small = false) {
     if (ps.empty()) return;
     std::stable_sort(ps.begin(), ps.end(),
                      [](const ConvProb& x, const ConvProb& y) { return (int64_t)x.K * x.splits > (int64_t)y.K * y.splits; });
@@ -910,8 +947,8 @@ static void build_tables(un_ctx* c, Tables& T) {
       total += (int64_t)p.tiles_m * p.tiles_n;
     }
     // halo forward passes that a multi-tile workgroup can run: mt consecutive
-    // m-tiles per workgroup
-    const int mt = kind == 7 ? (int)std::max<int64_t>(1, std::min<int64_t>(UN_HALO_MT, total / (UN_HALO_WPS * 2 * 256))) : 1;
+    // m-tiles per workgroup (small tiles: one)
+    const int mt = kind == 7 && !small ? (int)std::max<int64_t>(1, std::min<int64_t>(UN_HALO_MT, total / (UN_HALO_WPS * 2 * 256))) : 1;
     std::vector<TileGroup> gs;
     for (size_t k = 0; k < ps.size(); ++k) {
       ConvProb& p = ps[k];
@@ -958,8 +995,25 @@ static void build_tables(un_ctx* c, Tables& T) {
         (p.halo ? halo : plain).push_back(p);
         if (p.halo) lds = std::max(lds, halo_lds_bytes(p, bf ? 2 : 4, bf ? CONV_BK_BF16 : CONV_BK_F32, kind == 2));
       }
-      emit_conv_one(halo, out, kind == 1 ? 7 : 8, kclass);
-      if (!halo.empty()) out.back().lds = lds;
+      // few tiles: small ones, where every problem of the launch fits them (a
+      // problem's results do not depend on its tiles' shape)
+      int64_t tiles = 0;
+      for (auto& p : halo) tiles += (int64_t)p.tiles_m * cdiv(p.N, p.bn);
+      std::vector<ConvProb> small;
+      if (tiles <= (bf ? HALO_SMALL_MAX : HALO_SMALL_MAX_F32))
+        for (ConvProb p : halo)
+          if (try_halo_small(p, bf, kind == 2)) small.push_back(p);
+      const bool use_small = !halo.empty() && small.size() == halo.size();
+      if (use_small) {
+        halo = small;
+        lds = 0;
+        for (auto& p : halo) lds = std::max(lds, halo_lds_bytes(p, bf ? 2 : 4, bf ? CONV_BK_BF16 : CONV_BK_F32, kind == 2));
+      }
+      emit_conv_one(halo, out, kind == 1 ? 7 : 8, kclass, use_small);
+      if (!halo.empty()) {
+        out.back().lds = lds;
+        out.back().mode = use_small;
+      }
       emit_conv_one(plain, out, kind, kclass);
     } else {
       // weight gradient: one launch per code variant (pooled / unpooled with
@@ -1007,26 +1061,7 @@ static void build_tables(un_ctx* c, Tables& T) {
     out.push_back(Launch{kind, UN_K_ATTN, po, mo, (int)(map.size() / 2)});
     out.back().lds = lds;
   };
-  auto conv_base = [&](const Block& b) {
-    ConvProb p{};
-    p.Nb = c->groups[c->models[b.model].group].B;
-    p.C = b.C;
-    p.H = b.H;
-    p.W = b.W;
-    p.O = b.O;
-    p.KH = b.KH;
-    p.pad = b.pad;
-    p.OH = b.OH;
-    p.OW = b.OW;
-    p.PH = b.PH;
-    p.PW = b.PW;
-    p.pool = b.pool;
-    p.relu = b.relu;
-    p.prev_relu = b.prev_relu;
-    p.splits = 1;
-    p.mt = 1;
-    return p;
-  };
+  auto conv_base = [&](const Block& b) { return conv_geometry(b, c->groups[c->models[b.model].group].B); };
 
   // forward levels
   for (int lv = 0; lv < levels; ++lv) {
@@ -1774,7 +1809,17 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
   // launch of few enough tiles for the small tiles may come out of a full one
   // with large tiles: at most 4 x GEMM_SMALL_MAX entries, 4.3 times that with
   // the XCD padding (one run of 8 among 7 of 1), 8 bytes each)
-  c->tables_cap = 2 * T.host.size() + ((size_t)1 << 20) + (size_t)2 * levels * (18 * GEMM_SMALL_MAX + 64) * 8;
+  // The same goes for the halo conv launches: at most the small tiles of all.
+  size_t halo_small = 0;
+  for (auto& m : c->models)
+    for (auto& b : m.blocks)
+      for (int dg = 0; dg < 2 && b.kind == 1; ++dg) {
+        ConvProb p = conv_geometry(b, c->groups[m.group].B);
+        p.N = dg ? b.C : b.O;
+        p.K = b.KH * b.KH * (dg ? b.O : b.C);
+        if (try_halo_small(p, bf, dg != 0)) halo_small += (size_t)p.tiles_m * cdiv(p.N, p.bn) * 8;
+      }
+  c->tables_cap = halo_small + 2 * T.host.size() + ((size_t)1 << 20) + (size_t)2 * levels * (18 * GEMM_SMALL_MAX + 64) * 8;
   c->tables_off = A.take(c->tables_cap);
   c->bytes = A.top;
   if (dry) return UN_OK;
@@ -1970,7 +2015,7 @@ static hipError_t run_launch(un_ctx* c, const Launch& l, float lr) {
       break;
     case 7:
     case 8:
-      e = launch_conv_halo(c->bf16, l.kind == 8, c->at<ConvProb>(l.probs), c->at<int32_t>(l.map), l.count, l.lds,
+      e = launch_conv_halo(c->bf16, l.kind == 8, l.mode != 0, c->at<ConvProb>(l.probs), c->at<int32_t>(l.map), l.count, l.lds,
                            c->stream);
       break;
     case 4:
