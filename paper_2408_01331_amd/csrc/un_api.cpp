@@ -50,15 +50,16 @@ namespace {
 // 158 / 167, the 7 models 167 / 154 / 155 / 157 / 157.
 constexpr int HALO_SMALL_MAX = 1536, HALO_SMALL_MAX_F32 = 256;
 
-// A GEMM launch of at most this many large tiles (one per CU) runs small ones:
-// the launch then lasts as long as one tile's chain of k-blocks, and a small
-// tile's k-block reads a quarter of the LDS bytes and (fp32) runs a quarter of
-// the MFMAs. Steps with large tiles only / with this rule, in us: 2 fp32 MLPs
-// 56.5 / 37.4, 8 fp32 MLPs 103 / 69, 5 fp32 attention models 283 / 143, 12
-// bf16 MLPs with Adam 144 / 127, one bf16 MLP 165 / 141. With the line at 512
-// attn8 goes from 430 to 440 and the 64 MLPs from 769 to 774 us (two small
-// tiles per CU and more re-read operands beat one large one less often).
-constexpr int GEMM_SMALL_MAX = 256;
+// A GEMM launch of at most this many large tiles runs small ones: the launch
+// then lasts as long as one tile's chain of k-blocks, and a small tile's k-block
+// reads a quarter of the LDS bytes and (fp32) runs a quarter of the MFMAs. Steps
+// with large tiles only / with the line at 256, in us: 2 fp32 MLPs 56.5 / 37.4,
+// 8 fp32 MLPs 103 / 69, 5 fp32 attention models 283 / 143, 12 bf16 MLPs with
+// Adam 144 / 127, one bf16 MLP 165 / 141. The line at 256 / 384 / 512 / 768
+// (later, on the same code): the 64 bf16 MLPs 763 / 764 / 769 / 776, attn8 296 /
+// 296 / 297 / 300, 4 bf16 attention models 258 / 254 / 254 / 255; fp32: 8 MLPs
+// 66.7 / 66.7 / 66.5 / 65.0, 5 attention models of 48 tokens 277 / 270 / 270 / 270.
+constexpr int GEMM_SMALL_MAX = 384, GEMM_SMALL_MAX_F32 = 768;
 
 constexpr size_t NONE = ~(size_t)0;
 
@@ -842,7 +843,7 @@ static void build_tables(un_ctx* c, Tables& T) {
         large += (int64_t)cdiv(p.M, tl.bm) * (cdiv(p.N, tl.bn) + p.bias_tile) * (p.epi == EPI_WPART ? p.splits : 1);
         wide = wide || (p.ce_part && p.N > gemm_tile(bf, GEMM_SMALL).bn);
       }
-      if (large <= GEMM_SMALL_MAX) variant = wide ? GEMM_WIDE : GEMM_SMALL;
+      if (large <= (bf ? GEMM_SMALL_MAX : GEMM_SMALL_MAX_F32)) variant = wide ? GEMM_WIDE : GEMM_SMALL;
     }
     const int GBM = gemm_tile(bf, variant).bm, GBN = gemm_tile(bf, variant).bn;
     // k length of one tile: K, or one split's chunk
@@ -1816,7 +1817,7 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
   // --- allocate the arena: buffers + tables (room for the tables of any
   // active subset: never larger than twice the full set's, except that a
   // launch of few enough tiles for the small tiles may come out of a full one
-  // with large tiles: at most 4 x GEMM_SMALL_MAX entries, 4.3 times that with
+  // with large tiles: at most 4 x GEMM_SMALL_MAX_F32 entries, 4.3 times that with
   // the XCD padding (one run of 8 among 7 of 1), 8 bytes each)
   // The same goes for the halo conv launches: at most the small tiles of all.
   size_t halo_small = 0;
@@ -1828,7 +1829,7 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
         p.K = b.KH * b.KH * (dg ? b.O : b.C);
         if (try_halo_small(p, bf, dg != 0)) halo_small += (size_t)p.tiles_m * cdiv(p.N, p.bn) * 8;
       }
-  c->tables_cap = halo_small + 2 * T.host.size() + ((size_t)1 << 20) + (size_t)2 * levels * (18 * GEMM_SMALL_MAX + 64) * 8;
+  c->tables_cap = halo_small + 2 * T.host.size() + ((size_t)1 << 20) + (size_t)2 * levels * (18 * GEMM_SMALL_MAX_F32 + 64) * 8;
   c->tables_off = A.take(c->tables_cap);
   c->bytes = A.top;
   if (dry) return UN_OK;
