@@ -177,3 +177,34 @@ def test_set_params_refreshes_only_that_models_copies(name):
                 a.load_batch(x, y)
                 a.step(wl.lr)
             assert np.array_equal(_bits(a.get_params(0)), sh[1][0])
+
+
+def test_losses_of_more_contexts_than_the_slab_holds():
+    """The contexts' losses share a pinned slab of 256 units; contexts beyond it
+    have memory of their own, and freed units are used again."""
+    _need_gpu()
+    from paper_2408_01331_amd.unifiednn import Hybrid
+    spec = {"layers": [("linear", 10)], "num_classes": 10}
+    wl = W.Workload("slab", 1, 4, (8,), "f32", [spec], 0.1, 1, 2)
+    x, y = W.make_batch(wl, 0)
+
+    def one(seed):
+        h = Hybrid([spec], 4, (8,), "f32", seeds=[seed])
+        h.load_batch(x, y)
+        return h
+
+    hs = [one(s) for s in range(270)]
+    try:
+        for h in hs:
+            h.step(0.1, losses=False)
+        first = [float(h.step(0.1)[0]) for h in hs]
+        for h in hs[:200]:
+            h.close()
+        hs[:200] = [one(s) for s in range(200)]
+        for h in hs[:200]:
+            h.step(0.1, losses=False)
+        again = [float(h.step(0.1)[0]) for h in hs[:200]]
+        assert again == first[:200] and len(set(first)) > 200
+    finally:
+        for h in hs:
+            h.close()
