@@ -6,14 +6,17 @@
 //     for all models of one depth level in one launch: bf16 workgroups of 16
 //     waves, each wave a 32x32 tile of v_mfma_f32_32x32x16_bf16 on a 128x128
 //     workgroup tile; fp32 workgroups of 4 waves (2x2) of
-//     v_mfma_f32_16x16x4_f32 on 64x64;
+//     v_mfma_f32_16x16x4_f32 on 64x64; launches of few tiles on 64x64 and
+//     32x32 (GemmVar);
 //   - the implicit-GEMM convolution passes: forward with the bias / ReLU /
 //     2x2 max-pool epilogue and data gradient with the un-pool gather, on
 //     halo tiles staged in LDS (bf16: 8 waves of v_mfma_f32_32x32x16_bf16
 //     blocks, a lane's runs of four accumulator rows holding a pool window;
-//     the gathered passes for other shapes: 16x16x32), and the split-K weight
-//     gradient (bf16: the GEMM's 32x32x16 core on k-major operands), reduced
-//     in split order by a kernel that applies the update.
+//     launches of few tiles on tiles of 4 waves; the gathered passes for other
+//     shapes: 16x16x32), and the split-K weight gradient (the GEMM's core on
+//     k-major operands), reduced in split order by a kernel that applies the
+//     update;
+//   - in bf16, the self-attention core (16x16x32).
 // A workgroup owns one output tile of one problem (a halo forward workgroup
 // may own several consecutive m-tiles); a flat tile table maps blockIdx.x to
 // (problem, first tile). Every output element is reduced over k in a

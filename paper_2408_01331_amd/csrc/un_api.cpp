@@ -6,9 +6,12 @@
 // disjoint union of the sub-models' graphs with one global input):
 //   * every parameterised layer plus the ReLU / MaxPool that follow it becomes
 //     one fused block; block j of every model forms depth level j;
-//   * a step (Trainer, Algorithm 2) is: forward levels 0..L-1, one softmax-CE
-//     launch for all models, backward levels L-1..0 (dgrad and wgrad of one
-//     level share a launch), one multi-tensor SGD launch;
+//   * a step (Trainer, Algorithm 2) is: forward levels 0..L-1, the softmax-CE
+//     row pass of the models whose logits GEMM does not hold it, backward levels
+//     L-1..0 (Linear data gradients share a launch with the next level's Linear
+//     weight gradients and their updates; the loss sum rides in the first), the
+//     conv weight gradients of all levels, and one split-K reduction with the
+//     remaining updates;
 //   * the first hidden Linear layers of all models read the same input, so
 //     their weights live in one concatenated matrix and run as ONE GEMM.
 #include "../../include/unifiednn.h"
@@ -1265,9 +1268,10 @@ static void build_tables(un_ctx* c, Tables& T) {
   // gradients of level lv and the Linear weight gradients of level lv + 1
   // (at lv == 0 also those of level 0). A block's weights are updated one
   // launch after its data gradient has read them, so no launch both reads and
-  // writes the same weights. Conv blocks keep their own per-level launches
-  // (data gradient, then split-K weight gradient); the split-K reductions
-  // with their updates run in one launch after the last level.
+  // writes the same weights. Conv data gradients have launches of their own; the
+  // conv weight gradients of all levels, and then the split-K reductions with
+  // their updates, run after the last level.
+
   // columns of a weight-gradient product over K inputs: the weights and the
   // bias column, or the weights alone where they fill whole small tiles (by
   // the block's shape, not the launch's variant: the two sum the bias gradient
