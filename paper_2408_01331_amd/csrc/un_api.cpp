@@ -2313,7 +2313,8 @@ static hipError_t enqueue_step(un_ctx* c, float lr) {
     hipError_t e = run_launch(c, l, lr);
     if (e != hipSuccess) return e;
   }
-  hipError_t e = run_launch(c, c->ce, lr);
+  hipError_t e = hipSuccess;
+  if (c->ce.mode > 0) e = run_launch(c, c->ce, lr);  // no row pass where every model's CE is fused
   for (auto& l : c->bwd) {
     if (e != hipSuccess) return e;
     e = run_launch(c, l, lr);
