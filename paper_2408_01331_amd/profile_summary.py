@@ -4,9 +4,9 @@
         kernel table (calls, average/min/max microseconds, share) from the
         *_kernel_stats.csv of a `rocprofv3 --kernel-trace --stats` run
 
-    python -m paper_2408_01331_amd.profile_summary traffic --kernel NAME --workload W \\
+    python -m paper_2408_01331_amd.profile_summary traffic --kernel NAME [NAME ...] --workload W \\
         --fetch DIR --write DIR --copy-fetch DIR --copy-write DIR --out FILE
-        HBM bytes per launch of the kernels whose name contains NAME, from one
+        HBM bytes per launch of the kernels whose name contains a NAME, from one
         `rocprofv3 --pmc FETCH_SIZE` and one `--pmc WRITE_SIZE` run of the
         benchmark, each scaled by what the same counter reads for a plain
         elementwise copy of known size (`bench.py --copy-probe`)
@@ -87,13 +87,13 @@ def traffic(a):
     probe_bytes = 1 << 30
     ff = copy_factor(a.copy_fetch, "FETCH_SIZE", probe_bytes)
     wf = copy_factor(a.copy_write, "WRITE_SIZE", probe_bytes)
-    f = [v for n, v in per_dispatch(a.fetch, "FETCH_SIZE").values() if a.kernel in n]
-    w = [v for n, v in per_dispatch(a.write, "WRITE_SIZE").values() if a.kernel in n]
+    f = [v for n, v in per_dispatch(a.fetch, "FETCH_SIZE").values() if any(k in n for k in a.kernel)]
+    w = [v for n, v in per_dispatch(a.write, "WRITE_SIZE").values() if any(k in n for k in a.kernel)]
     if not f or not w:
-        sys.exit(f"no dispatch of {a.kernel}")
+        sys.exit(f"no dispatch of {' or '.join(a.kernel)}")
     fkib, wkib = sum(f) / len(f), sum(w) / len(w)
     rec = {
-        "kernel": a.kernel, "workload": a.workload,
+        "kernel": " + ".join(a.kernel), "workload": a.workload,
         "sources_sha256": sources_digest(),
         "dispatches": [len(f), len(w)],
         "fetch_kib_per_dispatch": fkib, "write_kib_per_dispatch": wkib,
@@ -186,7 +186,8 @@ def main():
     m.add_argument("--counters", nargs="+", required=True)
     m.add_argument("--match", nargs="+", default=["gemm_kernel", "conv_", "reduce_kernel", "elementwise"])
     t = sub.add_parser("traffic")
-    for k in ("kernel", "workload", "fetch", "write", "copy_fetch", "copy_write", "out"):
+    t.add_argument("--kernel", nargs="+", required=True)
+    for k in ("workload", "fetch", "write", "copy_fetch", "copy_write", "out"):
         t.add_argument("--" + k.replace("_", "-"), dest=k, required=True)
     a = ap.parse_args()
     if a.cmd == "stats":
