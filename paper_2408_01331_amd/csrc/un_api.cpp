@@ -2236,9 +2236,7 @@ un_status un_create_grouped(const un_model_spec* specs, int32_t n_models, const 
   un_status s = plan_and_alloc(c);
   if (s != UN_OK) {
     std::string msg = c->err.empty() ? g_create_error : c->err;
-    if (c->base) hipFree(c->base);
-    hipStreamDestroy(c->own_stream);
-    delete c;
+    un_destroy(c);  // whatever of it exists
     return fail(nullptr, s, msg);
   }
   std::vector<float> pt;
