@@ -81,7 +81,8 @@ typedef enum {
    * (PyTorch's Unflatten(1, (out, F / out)); F must divide). A Linear layer on
    * a sequence acts on every token (PyTorch's Linear on [B, T, d]); Flatten
    * turns a sequence back into T * d features, token by token. Allowed on the
-   * network input or on a Linear layer's flat output. Token features (the
+   * network input, on a Linear layer's flat output and on the channels of a
+   * flattened 1x1 map. Token features (the
    * result of UN_UNFLATTEN and every Linear on a sequence) must be a multiple
    * of 8. */
   UN_UNFLATTEN = 7,

@@ -345,7 +345,7 @@ void pad_channels(Model& m, int batch, int vec, int es) {
     if (b.kind == 1) {
       if (after_conv) b.C = m.blocks[j - 1].O;
       b.O = padded(b.O);
-    } else if (b.kind == 0 && after_conv) {
+    } else if (b.kind == 0 && after_conv && b.tokens == 1) {  // tokens of a 1x1 map are whole vectors already
       b.in_c = m.blocks[j - 1].O;
       b.K = b.in_c * b.in_h * b.in_w;
     }
@@ -493,7 +493,7 @@ un_status parse_model(const un_model_spec& s, const un_input_spec& in, int mi, M
       m.blocks.push_back(b);
     } else if (L.op == UN_UNFLATTEN) {
       if (seq || !(flat || (h == 1 && w == 1)) || !torch_order) {
-        why = where(i) + "unflatten reads the network's flat input or a Linear layer's flat output";
+        why = where(i) + "unflatten reads the network's flat input, a Linear layer's flat output or a 1x1 map";
         return UN_ERR_UNSUPPORTED;
       }
       const int F = c * h * w;
@@ -1412,7 +1412,7 @@ static void build_tables(un_ctx* c, Tables& T) {
           p.mask = ptr(b.X);  // the previous block's stored output, row-major
           p.ldmask = b.ldx;
           p.C = ptr(pb.G);
-          p.ldc = pb.kind == 1 ? pb.out_elems_per_sample() : pb.ldg * pb.tokens / b.tokens;
+          p.ldc = (pb.kind == 1 ? pb.out_elems_per_sample() : pb.ldg * pb.tokens) / b.tokens;
           if (b.res_to >= 0) {
             const Block& eb = m.blocks[b.res_to];
             p.R = ptr(eb.G);
@@ -1839,7 +1839,7 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
       } else {
         Block& p = m.blocks[j - 1];
         b.X = p.Y;
-        b.ldx = p.kind == 1 ? p.out_elems_per_sample() : p.ldy * p.tokens / b.tokens;
+        b.ldx = (p.kind == 1 ? p.out_elems_per_sample() : p.ldy * p.tokens) / b.tokens;
       }
     }
   }

@@ -43,7 +43,8 @@ int __hipPopCallConfiguration(dim3* g, dim3* b, size_t* s, void** st) { *g = cfg
 int hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t lds, void* st) {
   for (int i = 0; i < n_fns; ++i)
     if (fns[i].f == f && log_len + 512 < sizeof(log_buf))
-      log_len += snprintf(log_buf + log_len, 512, "%s %u %u %zu\n", fns[i].name, g.x, b.x, lds);
+      log_len += snprintf(log_buf + log_len, 512, "%s %u %u %zu %llu\n", fns[i].name, g.x, b.x, lds,
+                          (unsigned long long)*(uintptr_t*)args[0]);
   return 0;
 }
 /* memory */
@@ -86,14 +87,26 @@ from paper_2408_01331_amd import workloads as W
 U.lib()
 
 
+class Gemm(ctypes.Structure):  # the first fields of a grouped-GEMM problem
+    _fields_ = [(k, ctypes.c_int64) for k in ("A", "B", "lda", "ldb")] + [(k, ctypes.c_int32) for k in (
+        "M", "N", "K", "epi", "relu", "amode", "bmode", "tiles_n", "nsplit", "bias_tile", "model")] + [
+        ("C", ctypes.c_int64), ("ldc", ctypes.c_int64)]
+
+
 def launches():
-    return [l.split() for l in stub.stub_log().decode().splitlines()]
+    # (kernel, workgroups, threads, dynamic LDS, first argument) per launch since the last call
+    return [[l.split()[0]] + [int(v) for v in l.split()[1:]] for l in stub.stub_log().decode().splitlines()]
+
+
+def gemm_of(launch):
+    # the first problem of a grouped-GEMM launch
+    return Gemm.from_address(launch[4])
 """
 
 
 def run(code, tmp_path):
-    """Run `code` (which has `U`, `W`, `np`, `stub` and `launches()`) on the stub
-    and return the value it assigns to `result`."""
+    """Run `code` (which has `U`, `W`, `np`, `stub`, `launches()` on the stub
+    and `gemm_of()`) on the stub and return the value it assigns to `result`."""
     src, so = str(tmp_path / "stub.c"), str(tmp_path / "stub.so")
     if not os.path.exists(so):
         with open(src, "w") as f:

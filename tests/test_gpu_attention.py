@@ -123,3 +123,19 @@ def test_core_tile_edges(precision, T, d):
     m = [0, 1]
     orc, spread = run_oracle(wl, 1, m, spread=True)
     print(compare_step(wl, run_gpu(wl, 1), orc, m, spread=spread))
+
+
+@pytest.mark.parametrize("precision", ["f32", "bf16"])
+def test_tokens_of_a_one_pixel_map(precision):
+    """Conv layers down to a 1x1 map, whose channels are read as tokens by a
+    residual attention block, a plain attention layer and a Linear layer."""
+    _need_gpu()
+    conv = [("conv", 6, 3, 1), ("relu",), ("pool",), ("conv", 48, 4, 0), ("relu",), ("flatten",)]
+    tail = [("flatten",), ("linear", 10)]
+    specs = [{"layers": conv + [("unflatten", 3), ("res_begin",), ("attention",), ("res_end",), ("relu",)] + tail, "num_classes": 10},
+             {"layers": conv + [("unflatten", 6), ("attention",), ("linear", 24), ("relu",)] + tail, "num_classes": 10},
+             {"layers": conv + [("unflatten", 2), ("linear", 40), ("relu",)] + tail, "num_classes": 10}]
+    wl = W.Workload("onepixel", 3, 7, (3, 8, 8), precision, specs, 0.02, 1, 8, init="torch")
+    m = [0, 1, 2]
+    orc, spread = run_oracle(wl, 1, m, spread=True)
+    print(compare_step(wl, run_gpu(wl, 1), orc, m, spread=spread))

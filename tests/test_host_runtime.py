@@ -1,4 +1,6 @@
 """CPU tests of the runtime around the kernels, on the host HIP stub."""
+import pytest
+
 import _host_hip as H
 
 
@@ -20,3 +22,26 @@ U.un_destroy(a)
 result = [failed, stub.stub_device(), stub.stub_pinned()]
 """, tmp_path)
     assert res == [2, 0, 0]
+
+
+@pytest.mark.parametrize("precision", ["f32", "bf16"])
+def test_tokens_of_a_one_pixel_map(precision, tmp_path):
+    """A 1x1 map read as tokens: the token layer's width and row stride are a
+    token's, not the sample's (24 channels as 3 tokens of 8 features)."""
+    res = H.run("""
+spec = {"layers": [("conv", 24, 4, 0), ("relu",), ("flatten",), ("unflatten", 3), ("linear", 16), ("flatten",),
+                   ("linear", 5)], "num_classes": 5}
+h = U.Hybrid([spec], 6, (2, 4, 4), %r)
+h.load_batch(np.zeros((6, 2, 4, 4), np.float32), np.zeros(6, np.int32))
+launches()
+h.step(0.1)
+g = [l for l in launches() if "gemm_kernel" in l[0]]
+p = [gemm_of(l) for l in g]
+result = [(q.M, q.N, q.K, q.lda, q.ldb, q.ldc) for q in p]
+""" % precision, tmp_path)
+    # forward token layer and logits; backward by level: logits' data gradient,
+    # token layer's data gradient, token layer's weight gradient
+    assert res[0][:4] == [18, 16, 8, 8]
+    assert res[1][:4] == [6, 5, 48, 48]
+    assert res[3][:3] == [18, 8, 16] and res[3][5] == 8
+    assert res[4][:3] == [16, 9, 18] and res[4][3:5] == [16, 8]
