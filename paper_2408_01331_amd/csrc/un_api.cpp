@@ -1642,9 +1642,14 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
     // vectors (RGB, grey-scale) reads a copy of the input with zero channels
     // appended: its loaders then take whole vectors, and the padded weight
     // columns meet zeros only, so their gradient is exactly 0 and they stay 0.
-    g.in_cs = g.in_c;
-    if (any_conv0 && g.in_c % vec != 0) {
-      g.in_cs = (int)rup(g.in_c, vec);
+    // An input whose padded copy would outgrow the kernels' offsets is read as
+    // it is, element by element.
+    g.in_cs = (int)rup(g.in_c, vec);
+    for (auto& m : c->models)
+      if (m.group == (int)gi && m.blocks[0].kind == 1 && !conv_addressable(m.blocks[0], g.in_cs, m.blocks[0].O, B, es))
+        g.in_cs = g.in_c;
+    if (!any_conv0) g.in_cs = g.in_c;
+    if (g.in_cs != g.in_c) {
       g.XinC = A.take((size_t)B * g.in_h * g.in_w * g.in_cs * es);
       for (auto& m : c->models)
         if (m.group == (int)gi && m.blocks[0].kind == 1) m.blocks[0].C = g.in_cs;

@@ -125,3 +125,16 @@ def test_planner_takes_channels_it_cannot_pad():
     half, full = (un_plan_bytes([spec], b, (8, 512, 512), "bf16")[0] for b in (64, 128))
     # activation and gradient of the pooled one-channel map: 8 channels at batch 64, one at 128
     assert full < 2 * half - 2 * 64 * 512 * 512 * 2 * 6
+
+
+def test_planner_takes_an_input_it_cannot_pad():
+    """A one-channel bf16 input of 2^18 x 28 x 28 passes 2^31 bytes only when
+    padded to 8 channels (3.3 GB, of which the kernels would read the first
+    2^31 bytes): the group keeps its one channel, and no copy is made."""
+    from paper_2408_01331_amd.unifiednn import un_plan_bytes
+    spec = {"layers": [C(4, 5, 0), R, POOL, C(8, 3, 1), R, POOL, FLAT, L(10)], "num_classes": 10}
+    n = 1 << 18
+    small, full = (un_plan_bytes([spec], b, (1, 28, 28), "bf16")[0] for b in (n // 4, n))
+    pix = 28 * 28
+    # per sample: the staged fp32 batch, and the input in bf16: one channel, or 8
+    assert full < 4 * small - n * pix * 2 * 6
