@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2408_01331_amd import workloads as W
-from _parity import compare_run, compare_step, run_gpu, run_oracle
+from _parity import compare_run, compare_step, fro_err, run_gpu, run_oracle, tensor_err
 
 L, C, R, POOL, FLAT, RB, RE = (lambda n: ("linear", n)), (lambda *a: ("conv",) + a), ("relu",), ("pool",), \
     ("flatten",), ("res_begin",), ("res_end",)
@@ -114,6 +114,35 @@ def test_parameters_and_state_round_trip(kind):
         assert np.array_equal(la, lb)
         for i in range(a.n):
             assert np.array_equal(a.get_params(i), b.get_params(i))
+
+
+def unpadded(precision):
+    """A model whose rows of a padded channel count would pass 2^24 elements: it
+    runs with its own channels (1, 3, 1), element by element in every pass."""
+    spec = {"layers": [C(3, 3, 1), R, C(1, 3, 1), R, POOL, C(1, 1, 0), FLAT, L(10)], "num_classes": 10}
+    return W.Workload("unpadded", 1, 1, (1, 2, 1 << (21 if precision == "bf16" else 22)), precision, [spec], 0.02, 1, 4,
+                      init="torch")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["f32", "bf16"])
+def test_channels_that_are_not_padded(precision):
+    """The element-wise passes against the oracle. Some of the 2^22 ReLU and pool
+    decisions per channel lie within rounding of a tie; one that goes the other
+    way changes a gradient by one of 2^22 pixels' contributions, 2^-11 of its
+    norm where they are independent, so ten of them 1.6e-3 (bf16: the operands'
+    rounding, 2^-8, is more)."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = unpadded(precision)
+    tol, grad_tol = {"f32": (1e-4, 1e-2), "bf16": (2e-2, 2e-2)}[precision]
+    losses, params, grads = run_gpu(wl, 1)
+    lo, po, go, _ = run_oracle(wl, 1, [0])[0]
+    assert abs(losses[0, 0] - lo[0]) <= tol * abs(lo[0])
+    for t, (a, b, ga, gb) in enumerate(zip(params[0], po, grads[0], go)):
+        assert tensor_err(a, b) <= tol, t
+        assert fro_err(ga, gb) <= grad_tol, (t, fro_err(ga, gb))
 
 
 def test_planner_takes_channels_it_cannot_pad():

@@ -45,3 +45,19 @@ result = [(q.M, q.N, q.K, q.lda, q.ldb, q.ldc) for q in p]
     assert res[1][:4] == [6, 5, 48, 48]
     assert res[3][:3] == [18, 8, 16] and res[3][5] == 8
     assert res[4][:3] == [16, 9, 18] and res[4][3:5] == [16, 8]
+
+
+@pytest.mark.parametrize("precision", ["f32", "bf16"])
+def test_unpadded_channels_take_the_element_wise_passes(precision, tmp_path):
+    """test_conv_channels' model that cannot be padded runs what it is there for."""
+    res = H.run("""
+import test_conv_channels as T
+wl = T.unpadded(%r)
+h = U.Hybrid(wl.specs, wl.batch, wl.in_shape, wl.precision)
+h.load_batch(*W.make_batch(wl, 0))
+launches()
+h.step(0.1)
+result = [l[0] for l in launches() if "conv" in l[0]]
+""" % precision, tmp_path)
+    want = ["conv_fwd_kernel"] * 3 + ["conv_dgrad_kernel"] * 2 + ["conv_wgrad_kernel"]
+    assert len(res) == len(want) and all(w in r for w, r in zip(want, res)), res
