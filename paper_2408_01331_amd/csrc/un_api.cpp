@@ -109,7 +109,7 @@ struct Block {
   int splits = 1, kchunk = 0;
   // split-K of a long logits product (forward): its partials, summed by the
   // softmax-CE row pass
-  size_t fws = NONE, fws_size = 0;
+  size_t fws = NONE, fws_size = 0, fws_limit_size = 0;
   int64_t fldws = 0;
   int fsplits = 0, fkchunk = 0;
   // output geometry
@@ -1742,14 +1742,17 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
             // classes x splits, so many classes keep the fused CE. Depends
             // only on this block's shape.
             const int BKf = bf ? GEMM_BK_BF16 : GEMM_BK_F32, FKCH = bf ? 8 : 16;
-            const int nkbf = cdiv(b.K, BKf);
-            if (nkbf > FKCH && b.N <= 32 && b.tokens == 1) {  // rows = samples (the row pass's layout)
-              b.fsplits = cdiv(nkbf, FKCH);
-              b.fkchunk = cdiv(nkbf, b.fsplits);
-              b.fsplits = cdiv(nkbf, b.fkchunk);
-              b.fldws = rup(b.N, 4);
-              b.fws_size = (size_t)b.fsplits * R * b.fldws * 4;  // placed in the workspace range below
-            }
+            auto fcut = [&](int K, int& chunk) {  // splits of a product over K inputs; 0: not split
+              const int nkbf = cdiv(K, BKf);
+              if (nkbf <= FKCH || b.N > 32 || b.tokens != 1) return 0;  // rows = samples (the row pass's layout)
+              chunk = cdiv(nkbf, cdiv(nkbf, FKCH));
+              return cdiv(nkbf, chunk);
+            };
+            b.fsplits = fcut(b.K, b.fkchunk);
+            b.fldws = rup(b.N, 4);
+            b.fws_size = (size_t)b.fsplits * R * b.fldws * 4;  // placed in the workspace range below
+            int chunk;
+            b.fws_limit_size = (size_t)fcut(b.Kr, chunk) * R * b.fldws * 4;
           } else {
             b.ldy = rup(b.N, 8);
             b.Y = A.take((size_t)R * b.ldy * es);
@@ -1772,14 +1775,14 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
             const int kc = cdiv(nkb, cdiv(nkb, chunk));
             return std::make_pair(cdiv(nkb, kc), kc);
           };
-          auto part_bytes = [&](int splits) { return (size_t)splits * b.N * b.ldws * 4; };
           const int chunk = cdiv(b.N, u) * cdiv(b.K, u) <= 64 ? KCH_FEW : KCH;
           if (nkb > chunk) {
             std::tie(b.splits, b.kchunk) = cut(chunk);
-            b.ws_size = part_bytes(b.splits);  // placed in the workspace range below
+            b.ws_size = (size_t)b.splits * b.N * b.ldws * 4;  // placed in the workspace range below
           }
-          // its share of the size that un_step_scratch's limit is stated on
-          b.ws_limit_size = nkb > KCH ? part_bytes(cut(KCH).first) : 0;
+          // its share of the size that un_step_scratch's limit is stated on,
+          // which counts the model's own inputs
+          b.ws_limit_size = nkb > KCH ? (size_t)cut(KCH).first * b.N * rup(b.Kr + 1, 4) * 4 : 0;
         }
       } else {
         const int J = b.KH * b.KH * b.C;
@@ -1863,7 +1866,7 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
       if (b.ws_size) b.ws = A.take(b.ws_size);
       if (b.fws_size) b.fws = A.take(b.fws_size);
       if (b.ws_limit_size) lim.take(b.ws_limit_size);
-      if (b.fws_size) lim.take(b.fws_size);
+      if (b.fws_limit_size) lim.take(b.fws_limit_size);
     }
   c->ws_bytes = A.top - c->ws_lo;
   c->ws_limit_bytes = lim.top - c->ws_lo;

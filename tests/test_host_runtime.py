@@ -61,3 +61,27 @@ result = [l[0] for l in launches() if "conv" in l[0]]
 """ % precision, tmp_path)
     want = ["conv_fwd_kernel"] * 3 + ["conv_dgrad_kernel"] * 2 + ["conv_wgrad_kernel"]
     assert len(res) == len(want) and all(w in r for w, r in zip(want, res)), res
+
+
+def test_scratch_limit_counts_the_models_own_channels(tmp_path):
+    """un_step_scratch's limit counts a Linear layer's own inputs behind a conv
+    whose 9 channels are stored as 16: its weight gradient's 2 splits of 1500 x
+    2305 fit the 32 MiB array, of 1500 x 4097 they would not. The step runs; its
+    padded partials outgrow the array, so in the context's own workspace. One of
+    1500 x 4096 channels of its own is refused."""
+    res = H.run("""
+def status(channels):
+    spec = {"layers": [("conv", channels, 1, 0), ("relu",), ("flatten",), ("linear", 1500), ("relu",), ("linear", 4)],
+            "num_classes": 4}
+    h = U.Hybrid([spec], 1088, (8, 16, 16), "bf16")
+    h.load_batch(np.zeros((1088, 8, 16, 16), np.float32), np.zeros(1088, np.int32))
+    try:
+        U.un_step_scratch(h.ctx, 0.1, 1)
+    except U.UnError as e:
+        return e.status
+    return 0
+
+
+result = [status(9), status(16)]
+""", tmp_path)
+    assert res == [0, 7]
