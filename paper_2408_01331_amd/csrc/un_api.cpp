@@ -324,12 +324,42 @@ bool conv_addressable(const Block& b, int64_t C, int64_t O, int64_t batch, int64
   return biggest * es < lim && b.OW * O < row && b.W * C < row;
 }
 
+// The last conv's channels, padded, widen the Linear layer behind it: its three
+// products and its update grow by `extra` = N * (padded - own) weights per
+// flattened position, its memory by several times for one or two channels.
+// Unpadded, the conv's gradient passes run element by element, at a cost per conv
+// pixel that grows with the patch columns (and a data gradient, where there is
+// one) and with the channels read one by one. Both grow with the batch, in bf16
+// the Linear's share less (its update does not), hence the batch there.
+// Steps unpadded / padded, in us, of n models whose conv reads 3 x 32 x 32:
+// bf16, 1 channel, 4096 units, n = 4: 134 / 375 at batch 8, 187 / 409 at 64, 455 /
+// 563 at 256, 1456 / 1276 at 1024; 1024 units 93 / 147, 145 / 170, 400 / 229, 1339
+// / 581; 6 channels, 4096 units: 404 / 409 at 64, 789 / 565 at 256. fp32, 1
+// channel, n = 4 at batch 256, of 256 / 1024 / 4096 units: 242 / 182, 284 / 326,
+// 456 / 945; 6 channels 374 / 250, 587 / 536, 1514 / 1757; behind a conv of 16
+// channels, 2 channels, 4096 units 440 / 414, 1 channel, 16384 units 865 / 1204;
+// pooled, 6 channels of 28 x 28, 8192 units, n = 1, batch 32: 175 / 144. A widening
+// of few weights costs less than the element-wise passes' latency (bf16 16 x 16,
+// 512 units, n = 1: 74 / 55). What the line costs where it errs, of the cases
+// measured: one bf16 model of 2 pooled channels, 8192 units, batch 64 163 / 140;
+// one of 1 channel, 4096 units at batch 1024 stays padded at 432 / 482.
+bool widens_too_much(const Block& conv, const Block& lin, bool first, int batch, bool bf) {
+  const int vec = bf ? 8 : 4;
+  const int64_t extra = (int64_t)lin.N * (rup(conv.O, vec) - conv.O);
+  const int64_t cols = cdiv(conv.KH * conv.KH * (int64_t)conv.C + 1, bf ? CONV_BN_BF16 : CONV_BN_F32);
+  const int64_t passes = (cols + (first ? 0 : bf ? 4 : 1)) * (conv.pool ? 4 : 1);
+  if (extra * lin.in_h * lin.in_w < (bf ? 3 << 20 : 1 << 19)) return false;
+  return bf ? extra * (400 + batch) >= (32 + 8 * (int64_t)conv.O) * 1024 * batch * passes : extra >= (1500 + 500 * (int64_t)conv.O) * passes;
+}
+
 // Store a CNN's channels padded to whole 16-byte vectors: the vector loaders
 // and halo tiles then serve every channel count. A padded channel has zero
 // weights and bias, so its activation and gradient are zero, so every gradient
 // that involves it is exactly zero and under each optimizer it stays zero. A
 // model whose padded tensors would outgrow the kernels' offsets keeps its own
-// channel counts and the element-wise loaders.
+// channel counts and the element-wise loaders, and so does a last conv whose
+// padding costs its Linear layer more than it saves (unless its sum with a skip
+// input needs that input's channels).
 void pad_channels(Model& m, int batch, int vec, int es) {
   for (auto& b : m.blocks) b.Kr = b.K;
   auto padded = [&](int o) { return (int)rup(o, vec); };
@@ -344,7 +374,8 @@ void pad_channels(Model& m, int batch, int vec, int es) {
     const bool after_conv = j > 0 && m.blocks[j - 1].kind == 1;
     if (b.kind == 1) {
       if (after_conv) b.C = m.blocks[j - 1].O;
-      b.O = padded(b.O);
+      const Block& next = m.blocks[j + 1];  // the last block is a Linear
+      if (next.kind != 0 || b.res_from >= 0 || !widens_too_much(b, next, j == 0, batch, es == 2)) b.O = padded(b.O);
     } else if (b.kind == 0 && after_conv && b.tokens == 1) {  // tokens of a 1x1 map are whole vectors already
       b.in_c = m.blocks[j - 1].O;
       b.K = b.in_c * b.in_h * b.in_w;

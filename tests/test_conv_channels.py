@@ -167,3 +167,26 @@ def test_planner_takes_an_input_it_cannot_pad():
     pix = 28 * 28
     # per sample: the staged fp32 batch, and the input in bf16: one channel, or 8
     assert full < 4 * small - n * pix * 2 * 6
+
+
+def narrow_tails():
+    """Last convs of 1 and 2 channels (pooled and not, a first conv and a second)
+    in front of Linear layers so wide that the padded inputs would cost more than
+    the vector loaders save; and one whose skip keeps it padded."""
+    return [{"layers": sp + [FLAT, L(n), R, L(10)], "num_classes": 10} for sp, n in (
+        ([C(1, 3, 1), R], 1024),
+        ([C(8, 3, 1), R, POOL, C(1, 3, 1), R], 2560),
+        ([C(2, 5, 0), R, POOL], 10240),
+        ([C(1, 3, 1), R, RB, C(1, 3, 1), RE, R], 1024))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["f32", "bf16"])
+def test_narrow_conv_before_a_wide_linear(precision):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    for k, sp in enumerate(narrow_tails()):
+        wl = W.Workload("tail", 1, 8, (3, 32, 32), precision, [sp], 0.02, 1, 4, init="torch")
+        orc, spread = run_oracle(wl, 1, [0], spread=True)
+        print(k, compare_step(wl, run_gpu(wl, 1), orc, [0], spread=spread), flush=True)

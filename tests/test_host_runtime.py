@@ -85,3 +85,25 @@ def status(channels):
 result = [status(9), status(16)]
 """, tmp_path)
     assert res == [0, 7]
+
+
+@pytest.mark.parametrize("precision", ["f32", "bf16"])
+def test_narrow_conv_before_a_wide_linear_keeps_its_channels(precision, tmp_path):
+    """Its one channel is not stored as 4 (bf16: 8), which would widen the Linear
+    layer as much: the logits' and the wide layer's K in the forward pass, and the
+    bytes of the plan."""
+    res = H.run("""
+import test_conv_channels as T
+result = []
+for sp in T.narrow_tails():
+    h = U.Hybrid([sp], 8, (3, 32, 32), %r)
+    h.load_batch(np.zeros((8, 3, 32, 32), np.float32), np.zeros(8, np.int32))
+    launches()
+    h.step(0.1)
+    log = launches()
+    wide = gemm_of([l for l in log if "gemm_kernel" in l[0]][0])
+    result.append([wide.K, sum("conv_wgrad_kernel" in l[0] for l in log)])
+    h.close()
+""" % precision, tmp_path)
+    vec = 8 if precision == "bf16" else 4
+    assert res == [[1024, 1], [256, 1], [2 * 14 * 14, 1], [vec * 1024, 0]]
