@@ -53,16 +53,28 @@ namespace {
 // 158 / 167, the 7 models 167 / 154 / 155 / 157 / 157.
 constexpr int HALO_SMALL_MAX = 1536, HALO_SMALL_MAX_F32 = 256;
 
-// A GEMM launch of at most this many large tiles runs small ones: the launch
-// then lasts as long as one tile's chain of k-blocks, and a small tile's k-block
-// reads a quarter of the LDS bytes and (fp32) runs a quarter of the MFMAs. Steps
-// with large tiles only / with the line at 256, in us: 2 fp32 MLPs 56.5 / 37.4,
-// 8 fp32 MLPs 103 / 69, 5 fp32 attention models 283 / 143, 12 bf16 MLPs with
-// Adam 144 / 127, one bf16 MLP 165 / 141. The line at 256 / 384 / 512 / 768
-// (later, on the same code): the 64 bf16 MLPs 763 / 764 / 769 / 776, attn8 296 /
-// 296 / 297 / 300, 4 bf16 attention models 258 / 254 / 254 / 255; fp32: 8 MLPs
-// 66.7 / 66.7 / 66.5 / 65.0, 5 attention models of 48 tokens 277 / 270 / 270 / 270.
-constexpr int GEMM_SMALL_MAX = 384, GEMM_SMALL_MAX_F32 = 768;
+// A GEMM launch of few tiles runs small ones. Such a launch lasts as long as one
+// tile's chain of k-blocks, and a small tile's k-block reads a quarter of the LDS
+// bytes and (fp32) runs a quarter of the MFMAs; against it, a launch of small
+// tiles reads its operands twice as often. Steps with large tiles only / with
+// small ones up to 256 large tiles, in us: 2 fp32 MLPs 56.5 / 37.4, 8 fp32 MLPs
+// 103 / 69, 5 fp32 attention models 283 / 143, 12 bf16 MLPs with Adam 144 / 127,
+// one bf16 MLP 165 / 141.
+// bf16, in small tiles (a ragged problem's padding counts then as it costs):
+// forward launches of at most 512, two per CU, where the large tiles would leave
+// half of the CUs idle; from 192 large tiles on the second reading of the operands
+// costs more (3 hidden layers of width w, n models; a forward line of 512 / 768 /
+// 1020 / 1536 small tiles: w 1024, n 3, batch 1024 147 / 154 / 157 / 157; w 2048, n
+// 2, batch 1024 240 / 238 / 238 / 270; w 4096, n 4, batch 256 534 / 534 / 534 / 585; w
+// 4096, n 1, batch 1024 365 / 365 / 365 / 430; w 2048, n 1, batch 1024, of 512: 165,
+// large 170). In a backward launch a weight-gradient tile counts half: its update
+// epilogue, a large part of its time, is shorter in small tiles (a line of 640 /
+// 800 / 1100 so counted: w 1024, n 2, batch 1024 129 / 127 / 127; w 8192, n 1, batch
+// 128 481 / 481 / 481, large 506; w 1024, n 3 151 / 150 / 154; w 4096, n 1 371 / 371 /
+// 382; w 256, n 24, batch 512 108 / 107 / 100).
+// fp32, in large tiles, a line at 256 / 384 / 512 / 768: 8 MLPs 66.7 / 66.7 / 66.5 /
+// 65.0, 5 attention models of 48 tokens 277 / 270 / 270 / 270.
+constexpr int GEMM_SMALL_FWD = 512, GEMM_SMALL_BWD = 800, GEMM_SMALL_MAX_F32 = 768;
 
 constexpr size_t NONE = ~(size_t)0;
 
@@ -919,14 +931,19 @@ static void build_tables(un_ctx* c, Tables& T) {
     // element, never its value, so it may depend on the whole launch.
     int variant = GEMM_LARGE;
     {
-      int64_t large = 0;
+      int64_t large = 0, halves = 0;  // large tiles; half small tiles
       bool wide = false;
-      const GemmTile tl = gemm_tile(bf, GEMM_LARGE);
+      const GemmTile tl = gemm_tile(bf, GEMM_LARGE), ts = gemm_tile(bf, GEMM_SMALL);
+      const bool bwd = kclass == UN_K_GEMM_BWD;
       for (const GemmProb& p : ps) {
-        large += (int64_t)cdiv(p.M, tl.bm) * (cdiv(p.N, tl.bn) + p.bias_tile) * (p.epi == EPI_WPART ? p.splits : 1);
-        wide = wide || (p.ce_part && p.N > gemm_tile(bf, GEMM_SMALL).bn);
+        const int sp = p.epi == EPI_WPART ? p.splits : 1;
+        const bool wgrad = bwd && p.amode == OP_KMAJ;
+        large += (int64_t)cdiv(p.M, tl.bm) * (cdiv(p.N, tl.bn) + p.bias_tile) * sp;
+        halves += (int64_t)cdiv(p.M, ts.bm) * (cdiv(p.N, ts.bn) + p.bias_tile) * sp * (wgrad ? 1 : 2);
+        wide = wide || (p.ce_part && p.N > ts.bn);
       }
-      if (large <= (bf ? GEMM_SMALL_MAX : GEMM_SMALL_MAX_F32)) variant = wide ? GEMM_WIDE : GEMM_SMALL;
+      const bool few = bf ? halves <= 2 * (bwd ? GEMM_SMALL_BWD : GEMM_SMALL_FWD) : large <= GEMM_SMALL_MAX_F32;
+      if (few) variant = wide ? GEMM_WIDE : GEMM_SMALL;
     }
     const int GBM = gemm_tile(bf, variant).bm, GBN = gemm_tile(bf, variant).bn;
     // k length of one tile: K, or one split's chunk

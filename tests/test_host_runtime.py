@@ -107,3 +107,29 @@ for sp in T.narrow_tails():
 """ % precision, tmp_path)
     vec = 8 if precision == "bf16" else 4
     assert res == [[1024, 1], [256, 1], [2 * 14 * 14, 1], [vec * 1024, 0]]
+
+
+MLPS = """
+def variants(width, n, batch, classes=10):
+    layers = [x for w in [width] * 2 for x in (("linear", w), ("relu",))] + [("linear", classes)]
+    h = U.Hybrid([{"layers": layers, "num_classes": classes}] * n, batch, (1024,), "bf16")
+    h.load_batch(np.zeros((batch, 1024), np.float32), np.zeros(batch, np.int32))
+    launches()
+    h.step(0.1)
+    log = launches()
+    h.close()
+    return log
+"""
+
+
+def test_small_tiles_only_where_large_ones_leave_half_the_chip_idle(tmp_path):
+    """Forward launches of more than 512 small tiles take large ones (two bf16
+    layers of width w, n models, a batch: 4096, 1, 1024 has 1024 of them; 2048, 1, 960
+    at most 495), backward launches of more than 800 with weight gradients
+    counted half."""
+    res = H.run(MLPS + "result = [variants(4096, 1, 1024), variants(2048, 1, 960)]", tmp_path)
+    wide, narrow = [H.gemm_variants(log) for log in res]
+    # forward: two hidden layers, then the logits; backward: the logits' data
+    # gradient, the second layer's with the logits' weight gradient, and the rest
+    assert [v for b, v in wide if not b] == [0, 0, 1] and [v for b, v in wide if b] == [0, 0, 0]
+    assert [v for b, v in narrow if not b] == [1, 1, 1] and [v for b, v in narrow if b] == [1, 1, 0]
