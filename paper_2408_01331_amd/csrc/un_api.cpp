@@ -1812,9 +1812,15 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
           // split order by the step's reduction launch, which applies the
           // update. Depends only on this block's shape. A block of many tiles
           // takes chunks of at most 16 (fp32: 32) k-blocks, since every split
-          // writes and reads its partials; one of at most 64 small tiles leaves
-          // CUs idle and takes chunks of 8 (attn8 368 -> 353 us per step, 362
-          // with 4; 5 fp32 attention models 146 -> 118 us).
+          // writes and reads its partials; one of few small tiles leaves CUs
+          // idle and takes chunks of 8 (attn8 368 -> 353 us per step, 362 with
+          // 4; 5 fp32 attention models 146 -> 118 us). Few are 64 in fp32, 16
+          // in bf16, and 4 where chunks of 16 would not split at all: beside
+          // other models the split and its reduction cost more than the idle
+          // CUs (3 hidden layers, batch 768, 32 models, few = 64 / 16 / 4: width 384
+          // 260 / 199 / 197, 256 144 / 145 / 118, 192 117 / 116 / 103; one model 56 /
+          // 57 / 54, 51 / 51 / 54, 50 / 50 / 53; batch 8192, 8 models of 192 210 / 215 /
+          // 207; 4 attention models of width 96 136 / 135 / 145).
           const int BKg = bf ? GEMM_BK_BF16 : GEMM_BK_F32, u = gemm_tile(bf, GEMM_SMALL).bm;
           const int KCH = bf ? 16 : 32, KCH_FEW = 8;
           const int nkb = cdiv(R, BKg);
@@ -1823,7 +1829,8 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
             const int kc = cdiv(nkb, cdiv(nkb, chunk));
             return std::make_pair(cdiv(nkb, kc), kc);
           };
-          const int chunk = cdiv(b.N, u) * cdiv(b.K, u) <= 64 ? KCH_FEW : KCH;
+          const int few = !bf ? 64 : nkb > KCH ? 16 : 4;
+          const int chunk = (int64_t)cdiv(b.N, u) * cdiv(b.K, u) <= few ? KCH_FEW : KCH;
           if (nkb > chunk) {
             std::tie(b.splits, b.kchunk) = cut(chunk);
             b.ws_size = (size_t)b.splits * b.N * b.ldws * 4;  // placed in the workspace range below

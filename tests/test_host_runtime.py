@@ -133,3 +133,12 @@ def test_small_tiles_only_where_large_ones_leave_half_the_chip_idle(tmp_path):
     # gradient, the second layer's with the logits' weight gradient, and the rest
     assert [v for b, v in wide if not b] == [0, 0, 1] and [v for b, v in wide if b] == [0, 0, 0]
     assert [v for b, v in narrow if not b] == [1, 1, 1] and [v for b, v in narrow if b] == [1, 1, 0]
+
+
+def test_weight_gradients_that_one_chunk_holds_are_not_split(tmp_path):
+    """bf16 blocks of more than 4 small tiles at batch 768 (12 k-blocks, one chunk
+    of 16) take no partials and no reduction launch; longer batches split."""
+    res = H.run(MLPS + """
+result = [sum("reduce_kernel" in l[0] for l in variants(*a)) for a in ((256, 8, 768, 130), (256, 8, 2048, 130))]
+""", tmp_path)
+    assert res == [0, 1]
