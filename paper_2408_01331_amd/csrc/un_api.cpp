@@ -43,15 +43,27 @@ using namespace un;
 
 namespace {
 
-// A halo conv launch of at most this many tiles runs small ones: four per CU
-// in place of two, with a quarter of the rows to stage and of the k loop to wait
-// for each. Steps without / with small tiles up to 256 / 512 / 1024 / 1536
-// tiles, in us: resnet8 358 / 338 / 325 / 326 / 326; 7 bf16 models on 3
-// datasets 181 / 170 / 168 / 167 / 167; 11 bf16 CNNs on 28 x 28 118 / 115 / 110
-// / 109 / 102; cifar16's smallest launch has 1664 (with it small 1189 instead of
-// 1143). fp32 tiles are bound by their MFMAs sooner: 4 LeNets 161 / 156 / 158 /
-// 158 / 167, the 7 models 167 / 154 / 155 / 157 / 157.
-constexpr int HALO_SMALL_MAX = 1536, HALO_SMALL_MAX_F32 = 256;
+// When a halo conv launch runs small tiles (four per CU in place of two, with a
+// quarter of the rows to stage and of the k loop to wait for each). bf16:
+//   - the launch is so short that large tiles leave CUs idle: at most 256 tiles
+//     of 128 x 128 (a tall tile counts as two), and no more products than 256 of
+//     K = 1152. Beyond, the second reading of the weights costs more. Steps with
+//     no small tiles / a line at 256 / 512 / 1024 of any tiles, in us, of n models
+//     of three 3x3 convs of o channels: o 64, 32 x 32, n 1, batch 64 175 / 166 / 166 /
+//     166, batch 128 242 / 238 / 246 / 246, n 2 281 / 277 / 282 / 301; o 128, n 2, batch
+//     64 362 / 362 / 362 / 406; o 256, 16 x 16, n 2 575 / 564 / 602 / 604, n 4 684 / 684 /
+//     684 / 761; o 512, 8 x 8, n 2 598 / 567 / 571 / 568, n 4, batch 128 1098 / 1199 /
+//     1195 / 1323;
+//   - or small tiles waste at most half the products on columns and rows past the
+//     pass's own, up to 1536 tiles: passes of at most 32 columns, maps that fill
+//     little of a large tile. With 256 / 512 / 1024 / 1536: o 24, 24 x 24, n 8, batch
+//     64 171 / 168 / 157 / 148; o 16, 64 x 64, n 4, batch 32 208 / 206 / 205 / 205;
+//     resnet8 338 / 325 / 326 / 326; 11 CNNs on 28 x 28 115 / 110 / 109 / 102.
+// fp32 tiles are bound by their MFMAs sooner: 4 LeNets without / with small tiles
+// up to 256 / 512 / 1024 / 1536 161 / 156 / 158 / 158 / 167, 7 models on 3 datasets
+// 167 / 154 / 155 / 157 / 157, o 48, 20 x 20, n 4, batch 100 642 / 640 / 642 / 654 / 655.
+constexpr int64_t HALO_SMALL_AREA = 256 * 128 * 128;
+constexpr int HALO_SMALL_K = 1152, HALO_SMALL_MAX = 1536, HALO_SMALL_MAX_F32 = 256;
 
 // A GEMM launch of few tiles runs small ones. Such a launch lasts as long as one
 // tile's chain of k-blocks, and a small tile's k-block reads a quarter of the LDS
@@ -1098,13 +1110,22 @@ static void build_tables(un_ctx* c, Tables& T) {
       }
       // few tiles: small ones, where every problem of the launch fits them (a
       // problem's results do not depend on its tiles' shape)
-      int64_t tiles = 0;
-      for (auto& p : halo) tiles += (int64_t)p.tiles_m * cdiv(p.N, p.bn);
+      int64_t tiles = 0, area = 0;
+      double work = 0, work_small = 0;  // products, the padding's included
       std::vector<ConvProb> small;
-      if (tiles <= (bf ? HALO_SMALL_MAX : HALO_SMALL_MAX_F32))
-        for (ConvProb p : halo)
-          if (try_halo_small(p, bf, kind == 2)) small.push_back(p);
-      const bool use_small = !halo.empty() && small.size() == halo.size();
+      for (ConvProb p : halo) {
+        const int64_t n = (int64_t)p.tiles_m * cdiv(p.N, p.bn);
+        tiles += n;
+        area += n * p.bm * p.bn;
+        work += (double)n * p.bm * p.bn * p.K;
+        if (!try_halo_small(p, bf, kind == 2)) continue;
+        small.push_back(p);
+        work_small += (double)p.tiles_m * cdiv(p.N, p.bn) * p.bm * p.bn * p.K;
+      }
+      const bool few = !bf ? tiles <= HALO_SMALL_MAX_F32
+                           : (area <= HALO_SMALL_AREA && work_small <= (double)HALO_SMALL_AREA * HALO_SMALL_K) ||
+                                 (tiles <= HALO_SMALL_MAX && 2 * work_small <= work);
+      const bool use_small = few && !halo.empty() && small.size() == halo.size();
       if (use_small) {
         halo = small;
         lds = 0;

@@ -142,3 +142,25 @@ def test_weight_gradients_that_one_chunk_holds_are_not_split(tmp_path):
 result = [sum("reduce_kernel" in l[0] for l in variants(*a)) for a in ((256, 8, 768, 130), (256, 8, 2048, 130))]
 """, tmp_path)
     assert res == [0, 1]
+
+
+def test_small_conv_tiles_only_for_short_or_badly_filled_launches(tmp_path):
+    """bf16 halo launches: 32 x 32 maps of 64 channels at batch 64 (256 tiles' area)
+    take small tiles and at batch 128 large ones; 24 channels on 24 x 24, whose
+    large tiles are mostly padding, small ones."""
+    res = H.run("""
+def convs(o, side, n, batch):
+    spec = {"layers": [("conv", o, 3, 1), ("relu",), ("conv", o, 3, 1), ("relu",), ("pool",), ("flatten",), ("linear", 10)],
+            "num_classes": 10}
+    h = U.Hybrid([spec] * n, batch, (3, side, side), "bf16")
+    h.load_batch(np.zeros((batch, 3, side, side), np.float32), np.zeros(batch, np.int32))
+    launches()
+    h.step(0.1)
+    out = ["small" if "conv_halo_small" in l[0] else "large" for l in launches() if "conv_halo" in l[0]]
+    h.close()
+    return out
+
+
+result = [convs(64, 32, 1, 64), convs(64, 32, 1, 128), convs(24, 24, 8, 64)]
+""", tmp_path)
+    assert res == [["small"] * 3, ["large"] * 3, ["small"] * 3]
