@@ -66,21 +66,26 @@ def test_row_tiles_that_rows_do_not_fill(precision, side, batch):
     print(compare_step(wl, run_gpu(wl, 1), orc, m, spread=spread))
 
 
+def tiles(precision, k, c1, c2):
+    """k equal models of three convs."""
+    spec = {"layers": [C(c1, 3, 1), R, POOL, C(c2, 3, 1), R, C(16, 3, 1), R, POOL, FLAT, L(10)], "num_classes": 10}
+    return W.Workload("tiles", k, 16, (3, 24, 24), precision, [spec] * k, 0.02, 2, 4, init="torch")
+
+
+TILES = [("f32", 40), ("bf16", 120)], [(8, 24), (33, 72)]
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("precision,n", [("f32", 40), ("bf16", 120)])
-@pytest.mark.parametrize("c1,c2", [(8, 24), (33, 72)])
+@pytest.mark.parametrize("precision,n", TILES[0])
+@pytest.mark.parametrize("c1,c2", TILES[1])
 def test_small_and_large_conv_tiles_agree(precision, n, c1, c2):
     """A model alone (small conv tiles) against the same model beside so many
     others that every conv launch takes the large ones: bit for bit."""
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    spec = {"layers": [C(c1, 3, 1), R, POOL, C(c2, 3, 1), R, C(16, 3, 1), R, POOL, FLAT, L(10)], "num_classes": 10}
-
-    def wl(k):
-        return W.Workload("tiles", k, 16, (3, 24, 24), precision, [spec] * k, 0.02, 2, 4, init="torch")
-
-    solo, merged = run_gpu(wl(1), 2), run_gpu(wl(n), 2, models=[0])
+    solo = run_gpu(tiles(precision, 1, c1, c2), 2)
+    merged = run_gpu(tiles(precision, n, c1, c2), 2, models=[0])
     for a, b in zip([merged[0][:, 0]] + merged[1][0] + merged[2][0], [solo[0][:, 0]] + solo[1][0] + solo[2][0]):
         assert np.array_equal(np.asarray(a, np.float32).view(np.uint32), np.asarray(b, np.float32).view(np.uint32))
 

@@ -5,9 +5,15 @@ import numpy as np
 import pytest
 
 from paper_2408_01331_amd import workloads as W
-from _parity import run_gpu
+from _parity import compare_step, run_gpu, run_oracle
 
 pytestmark = pytest.mark.gpu
+
+
+def _need_gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
 
 
 def _mlp(widths, classes):
@@ -19,9 +25,24 @@ def _mlp(widths, classes):
 
 # (batch, classes, widths): tile edges +- 1, one row, a k-block remainder, classes
 # of one small tile, of more than one (fused over the large width) and of more
-# than a large one (separate softmax-CE pass)
+# than a large one (separate softmax-CE pass); widths of whole small tiles, whose
+# bias gradient is summed on its own, with a k remainder and split over k
 CASES = [(1, 10, [8]), (31, 33, [33]), (32, 32, [65, 31]), (33, 64, [64, 127]), (65, 65, [129, 63]),
-         (127, 100, [72, 40]), (129, 130, [128, 257])]
+         (127, 100, [72, 40]), (129, 130, [128, 257]), (200, 10, [128, 64]), (700, 10, [128, 64])]
+
+
+def models(batch, classes, widths, precision, alone):
+    """The case's model, alone or as the first beside 350 others with one hidden
+    level more, enough that every launch that it takes part in has large tiles
+    (test_host_runtime checks the variants)."""
+    specs = [_mlp(widths, classes)]
+    if not alone:
+        specs += [_mlp([136] * (len(widths) + 1), classes) for _ in range(350)]
+    return W.Workload("t", len(specs), batch, (104,), precision, specs, 0.05, 2, 9)
+
+
+def _same(a, b):
+    assert np.array_equal(np.asarray(a, np.float32).view(np.uint32), np.asarray(b, np.float32).view(np.uint32))
 
 
 @pytest.mark.parametrize("precision", ["f32", "bf16"])
@@ -29,30 +50,41 @@ CASES = [(1, 10, [8]), (31, 33, [33]), (32, 32, [65, 31]), (33, 64, [64, 127]), 
 def test_alone_equals_in_a_large_launch(precision, batch, classes, widths):
     """The model alone (small tiles) against the same model beside enough others
     that every one of its launches takes large tiles: losses, parameters and
-    gradients."""
-    torch = pytest.importorskip("torch")
-    if not torch.cuda.is_available():
-        pytest.skip("no GPU")
-    spec = _mlp(widths, classes)
-    # one hidden level more than the model, and over 256 large tiles at each
-    big = [_mlp([136] * (len(widths) + 1), classes) for _ in range(260)]
-    specs = [spec] + big
-
-    def wl(sp):
-        return W.Workload("t", len(sp), batch, (104,), precision, sp, 0.05, 2, 9)
-
-    alone = run_gpu(wl([spec]), 2)
-    merged = run_gpu(wl(specs), 2, models=[0])
-    assert np.array_equal(alone[0][:, 0].view(np.uint32), merged[0][:, 0].view(np.uint32))
+    gradients, bit for bit; and alone against the oracle."""
+    _need_gpu()
+    case = (batch, classes, widths, precision)
+    alone = run_gpu(models(*case, True), 2)
+    merged = run_gpu(models(*case, False), 2, models=[0])
+    _same(alone[0][:, 0], merged[0][:, 0])
     for a, b in zip(alone[1][0] + alone[2][0], merged[1][0] + merged[2][0]):
-        assert np.array_equal(np.asarray(a, np.float32).view(np.uint32), np.asarray(b, np.float32).view(np.uint32))
-    if precision == "bf16":
-        return
-    # and against the oracle (one step's loss)
-    import oracle
-    x, y = W.make_batch(wl([spec]), 0)
-    lo, _, _ = oracle.step(spec, W.init_params(spec, (104,), 9, 0), x, y, 0.05, precision)
-    assert abs(alone[0][0, 0] - lo) <= 1e-5 * abs(lo)
+        _same(a, b)
+    orc, spread = run_oracle(models(*case, True), 1, [0], spread=True)
+    print(compare_step(models(*case, True), run_gpu(models(*case, True), 1), orc, [0], spread=spread))
+
+
+@pytest.mark.parametrize("precision", ["f32", "bf16"])
+@pytest.mark.parametrize("kind", ["momentum", "adam"])
+@pytest.mark.parametrize("batch,classes,widths", [(33, 64, [64, 127]), (129, 130, [128, 257]), (700, 10, [128, 64])])
+def test_optimizer_epilogues_agree(precision, kind, batch, classes, widths):
+    """The same under momentum and Adam with a rate per model; the models beside
+    it take SGD, momentum and Adam in turn, so a large launch's first-layer
+    weight gradient mixes them over its rows: parameters and optimizer state."""
+    _need_gpu()
+    from paper_2408_01331_amd.unifiednn import Hybrid, flatten_params
+    out = []
+    for alone in (True, False):
+        wl = models(batch, classes, widths, precision, alone)
+        with Hybrid(wl.specs, wl.batch, wl.in_shape, wl.precision) as h:
+            for i in range(wl.n_models):
+                h.set_params(i, flatten_params(W.init_params(wl.specs[i], wl.in_shape, wl.seed, i, wl.init)))
+                h.set_optimizer(i, kind if i == 0 else ("sgd", "momentum", "adam")[i % 3], momentum=0.9)
+            rates = 1e-3 * (1 + np.arange(wl.n_models) % 5).astype(np.float32)
+            for step in range(3):
+                h.load_batch(*W.make_batch(wl, step))
+                h.step(rates)
+            out.append((h.get_params(0), h.get_opt_state(0)[0]))
+    for a, b in zip(*out):
+        _same(a, b)
 
 
 def test_scratch_step_beyond_the_array():

@@ -164,3 +164,44 @@ def convs(o, side, n, batch):
 result = [convs(64, 32, 1, 64), convs(64, 32, 1, 128), convs(24, 24, 8, 64)]
 """, tmp_path)
     assert res == [["small"] * 3, ["large"] * 3, ["small"] * 3]
+
+
+def test_tile_variants_that_the_gpu_tests_compare(tmp_path):
+    """test_gpu_gemm_tiles and test_conv_channels compare a model alone with one
+    beside others: alone every launch takes small (or wide) tiles, beside the
+    others every launch that the model takes part in large ones."""
+    res = H.run("""
+import test_conv_channels as TC
+import test_gpu_gemm_tiles as T
+
+
+def log(wl):
+    h = U.Hybrid(wl.specs, wl.batch, wl.in_shape, wl.precision)
+    h.load_batch(*W.make_batch(wl, 0))
+    launches()
+    h.step(0.1)
+    out = launches()
+    h.close()
+    return out
+
+
+result = [[[log(T.models(*c, p, alone)) for alone in (True, False)] for c in T.CASES] for p in ("f32", "bf16")]
+conv = [[["small" in l[0] for l in log(TC.tiles(p, k, *c)) if "conv_halo" in l[0]] for k in (1, n)]
+        for p, n in TC.TILES[0] for c in TC.TILES[1]]
+result = [result, conv]
+""", tmp_path)
+    res, conv = res
+    for alone, merged in conv:
+        # (two rows of 24 pixels, which a pooled pass needs, are no small fp32 tile of 32 x 32)
+        assert len(alone) == len(merged) == 5 and all(alone[1:]) and not any(merged)
+    import test_gpu_gemm_tiles as T
+    wide = 0
+    for by_case in res:
+        for (batch, classes, widths), (alone, merged) in zip(T.CASES, by_case):
+            a, m = H.gemm_variants(alone), H.gemm_variants(merged)
+            assert all(v != 0 for _, v in a), (batch, classes, widths)
+            wide += sum(v == 2 for _, v in a)
+            # forward: the model's levels; backward: all but the others' deepest
+            assert all(v == 0 for _, v in [x for x in m if not x[0]][:len(widths) + 1]), (batch, classes, widths)
+            assert all(v == 0 for _, v in [x for x in m if x[0]]), (batch, classes, widths)
+    assert wide > 0
