@@ -63,12 +63,13 @@ def test_alone_equals_in_a_large_launch(precision, batch, classes, widths):
 
 
 @pytest.mark.parametrize("precision", ["f32", "bf16"])
-@pytest.mark.parametrize("kind", ["momentum", "adam"])
+@pytest.mark.parametrize("kind", ["sgd", "momentum", "adam"])
 @pytest.mark.parametrize("batch,classes,widths", [(33, 64, [64, 127]), (129, 130, [128, 257]), (700, 10, [128, 64])])
 def test_optimizer_epilogues_agree(precision, kind, batch, classes, widths):
-    """The same under momentum and Adam with a rate per model; the models beside
-    it take SGD, momentum and Adam in turn, so a large launch's first-layer
-    weight gradient mixes them over its rows: parameters and optimizer state."""
+    """The same with a rate per model, under SGD beside SGD models, and under
+    momentum and Adam beside models of all three kinds in turn, so that a large
+    launch's first-layer weight gradient mixes them over its rows: parameters and
+    optimizer state."""
     _need_gpu()
     from paper_2408_01331_amd.unifiednn import Hybrid, flatten_params
     out = []
@@ -77,7 +78,8 @@ def test_optimizer_epilogues_agree(precision, kind, batch, classes, widths):
         with Hybrid(wl.specs, wl.batch, wl.in_shape, wl.precision) as h:
             for i in range(wl.n_models):
                 h.set_params(i, flatten_params(W.init_params(wl.specs[i], wl.in_shape, wl.seed, i, wl.init)))
-                h.set_optimizer(i, kind if i == 0 else ("sgd", "momentum", "adam")[i % 3], momentum=0.9)
+                if kind != "sgd":
+                    h.set_optimizer(i, kind if i == 0 else ("sgd", "momentum", "adam")[i % 3], momentum=0.9)
             rates = 1e-3 * (1 + np.arange(wl.n_models) % 5).astype(np.float32)
             for step in range(3):
                 h.load_batch(*W.make_batch(wl, step))
