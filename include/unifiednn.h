@@ -93,7 +93,7 @@ typedef enum {
    * order: in_proj_weight [3d, d], in_proj_bias [3d], out_proj.weight
    * [d, d], out_proj.bias [d]. A ReLU may follow, and residual markers may
    * enclose it (x + attn(x)). T <= 64 and the per-sample working set
-   * (4 T (d + 1) + 2 T (T + 1) floats) must fit 160 KiB of LDS. */
+   * (4 T (d + 4) + 2 T (T + 1) floats) must fit 160 KiB of LDS. */
   UN_SELF_ATTENTION = 8
 } un_op;
 

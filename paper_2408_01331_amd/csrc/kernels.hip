@@ -3106,38 +3106,27 @@ __global__ __launch_bounds__(CE_ROWS * CE_LANES) void ce_rows_kernel(const CePro
 // order, and the softmax row reductions are fixed lane-shuffle butterflies.
 // (bf16 storage: attn_fwd_mfma_kernel, attn_bwd_mfma_kernel below.)
 // ---------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ void attn_stage(const AttnProb& p, int b, T* sQ, T* sK, T* sV) {
-  // Q | K | V rows of 3d elements, copied as 16-byte vectors (d is a multiple
-  // of 8) into LDS rows of d plus one 16-byte chunk, in the storage type
-  constexpr int VEC = TT<T>::VEC;
+__device__ __forceinline__ void attn_stage(const AttnProb& p, int b, float* sQ, float* sK, float* sV) {
+  // Q | K | V rows of 3d floats, copied as 16-byte vectors (d is a multiple of
+  // 8) into LDS rows of d plus one 16-byte chunk
+  constexpr int VEC = 4;
   const int Tn = p.T, d = p.d, ld = d + VEC, vpr = d / VEC;
-  const T* qkv = (const T*)p.QKV + (int64_t)b * Tn * p.ldq;
+  const float* qkv = (const float*)p.QKV + (int64_t)b * Tn * p.ldq;
   for (int e = threadIdx.x; e < Tn * vpr; e += blockDim.x) {
     const int t = e / vpr, j = (e - t * vpr) * VEC;
-    const T* row = qkv + (int64_t)t * p.ldq + j;
+    const float* row = qkv + (int64_t)t * p.ldq + j;
     *(u32x4*)(sQ + t * ld + j) = *(gptr<const u32x4>)row;
     *(u32x4*)(sK + t * ld + j) = *(gptr<const u32x4>)(row + d);
     *(u32x4*)(sV + t * ld + j) = *(gptr<const u32x4>)(row + 2 * d);
   }
 }
 
-// Four consecutive values of a row to global memory as one store (bf16: 8
-// bytes, fp32: 16), or element by element at a row's end.
-template <typename T>
-__device__ __forceinline__ void attn_put4(T* dst, const float* v, int n, float scale) {
-  if (n == 4) {
-    if constexpr (sizeof(T) == 2) {
-      u32x2 w;
-      w[0] = f2bf2(v[0] * scale, v[1] * scale);
-      w[1] = f2bf2(v[2] * scale, v[3] * scale);
-      *(gptr<u32x2>)dst = w;
-    } else {
-      *(gptr<f32x4>)dst = f32x4{v[0] * scale, v[1] * scale, v[2] * scale, v[3] * scale};
-    }
-  } else {
-    for (int e = 0; e < n; ++e) dst[e] = TT<T>::from_f(v[e] * scale);
-  }
+// Four consecutive values of a row to global memory as one 16-byte store, or
+// element by element at a row's end.
+__device__ __forceinline__ void attn_put4(float* dst, const float* v, int n, float scale) {
+  if (n == 4) *(gptr<f32x4>)dst = f32x4{v[0] * scale, v[1] * scale, v[2] * scale, v[3] * scale};
+  else
+    for (int e = 0; e < n; ++e) dst[e] = v[e] * scale;
 }
 
 // out[r][c] = sum over x of a(r, x) * b(c, x) for r < rows, c < cols: each
@@ -3180,23 +3169,22 @@ __device__ __forceinline__ void attn_products(int rows, int cols, int n, FA&& fa
   }
 }
 
-template <typename T>
 __global__ __launch_bounds__(256) void attn_fwd_kernel(const AttnProb* __restrict__ probs,
                                                        const int32_t* __restrict__ tile_map) {
   extern __shared__ float sm[];
   const int pi = tile_map[2 * blockIdx.x], b = tile_map[2 * blockIdx.x + 1];
   if (pi < 0) return;
   const AttnProb& p = probs[pi];
-  const int Tn = p.T, d = p.d, ld = d + TT<T>::VEC, ls = Tn + 1;
-  T* sQ = (T*)sm;  // Q, K, V rows in the storage type, then [T][T + 1] fp32 scores
-  T* sK = sQ + Tn * ld;
-  T* sV = sK + Tn * ld;
-  float* sS = (float*)(sV + Tn * ld);
-  attn_stage<T>(p, b, sQ, sK, sV);
+  const int Tn = p.T, d = p.d, ld = d + 4, ls = Tn + 1;
+  float* sQ = sm;  // Q, K, V rows, then [T][T + 1] scores
+  float* sK = sQ + Tn * ld;
+  float* sV = sK + Tn * ld;
+  float* sS = sV + Tn * ld;
+  attn_stage(p, b, sQ, sK, sV);
   __syncthreads();
   // S[i][t] = (Q K^T)[i][t] * scale
-  attn_products<2, 2>(Tn, Tn, d, [&](int i, int k) { return TT<T>::to_f(sQ[i * ld + k]); },
-                      [&](int t, int k) { return TT<T>::to_f(sK[t * ld + k]); },
+  attn_products<2, 2>(Tn, Tn, d, [&](int i, int k) { return sQ[i * ld + k]; },
+                      [&](int t, int k) { return sK[t * ld + k]; },
                       [&](int i, int t0, const float* v, int n) {
                         for (int e = 0; e < n; ++e) sS[i * ls + t0 + e] = v[e] * p.scale;
                       });
@@ -3217,29 +3205,28 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(const AttnProb* __restric
   }
   __syncthreads();
   // A[i][j] = (P V)[i][j]
-  T* A = (T*)p.A + (int64_t)b * Tn * p.lda;
+  float* A = (float*)p.A + (int64_t)b * Tn * p.lda;
   attn_products<4, 4>(Tn, d, Tn, [&](int i, int t) { return sS[i * ls + t]; },
-                      [&](int j, int t) { return TT<T>::to_f(sV[t * ld + j]); },
-                      [&](int i, int j0, const float* v, int n) { attn_put4<T>(A + (int64_t)i * p.lda + j0, v, n, 1.f); });
+                      [&](int j, int t) { return sV[t * ld + j]; },
+                      [&](int i, int j0, const float* v, int n) { attn_put4(A + (int64_t)i * p.lda + j0, v, n, 1.f); });
 }
 
-template <typename T>
 __global__ __launch_bounds__(256) void attn_bwd_kernel(const AttnProb* __restrict__ probs,
                                                        const int32_t* __restrict__ tile_map) {
   extern __shared__ float sm[];
   const int pi = tile_map[2 * blockIdx.x], b = tile_map[2 * blockIdx.x + 1];
   if (pi < 0) return;
   const AttnProb& p = probs[pi];
-  constexpr int VEC = TT<T>::VEC;
+  constexpr int VEC = 4;
   const int Tn = p.T, d = p.d, ld = d + VEC, ls = Tn + 1;
-  T* sQ = (T*)sm;  // Q, K, V, dA rows in the storage type, then two fp32 tiles
-  T* sK = sQ + Tn * ld;
-  T* sV = sK + Tn * ld;
-  T* sD = sV + Tn * ld;                       // dA
-  float* sP = (float*)(sD + Tn * ld);         // [T][T + 1] probabilities
+  float* sQ = sm;  // Q, K, V, dA rows, then two tiles
+  float* sK = sQ + Tn * ld;
+  float* sV = sK + Tn * ld;
+  float* sD = sV + Tn * ld;                       // dA
+  float* sP = sD + Tn * ld;                  // [T][T + 1] probabilities
   float* sG = sP + Tn * ls;                   // [T][T + 1] dP, then dS
-  attn_stage<T>(p, b, sQ, sK, sV);
-  const T* dA = (const T*)p.dA + (int64_t)b * Tn * p.lda;
+  attn_stage(p, b, sQ, sK, sV);
+  const float* dA = (const float*)p.dA + (int64_t)b * Tn * p.lda;
   const float* Pg = p.P + (int64_t)b * Tn * Tn;
   {
     const int vpr = d / VEC;
@@ -3254,8 +3241,8 @@ __global__ __launch_bounds__(256) void attn_bwd_kernel(const AttnProb* __restric
   }
   __syncthreads();
   // dP[i][t] = sum_j dA[i][j] V[t][j]
-  attn_products<2, 2>(Tn, Tn, d, [&](int i, int j) { return TT<T>::to_f(sD[i * ld + j]); },
-                      [&](int t, int j) { return TT<T>::to_f(sV[t * ld + j]); },
+  attn_products<2, 2>(Tn, Tn, d, [&](int i, int j) { return sD[i * ld + j]; },
+                      [&](int t, int j) { return sV[t * ld + j]; },
                       [&](int i, int t0, const float* v, int n) {
                         for (int e = 0; e < n; ++e) sG[i * ls + t0 + e] = v[e];
                       });
@@ -3269,22 +3256,22 @@ __global__ __launch_bounds__(256) void attn_bwd_kernel(const AttnProb* __restric
     if (lane < Tn) sG[i * ls + lane] = pr * (dp - rd);
   }
   __syncthreads();
-  T* dqkv = (T*)p.dQKV + (int64_t)b * Tn * p.ldq;
+  float* dqkv = (float*)p.dQKV + (int64_t)b * Tn * p.ldq;
   // dQ[r][k] = scale * sum_t dS[r][t] K[t][k]
   attn_products<4, 4>(Tn, d, Tn, [&](int r, int t) { return sG[r * ls + t]; },
-                      [&](int k, int t) { return TT<T>::to_f(sK[t * ld + k]); },
-                      [&](int r, int k0, const float* v, int n) { attn_put4<T>(dqkv + (int64_t)r * p.ldq + k0, v, n, p.scale); });
+                      [&](int k, int t) { return sK[t * ld + k]; },
+                      [&](int r, int k0, const float* v, int n) { attn_put4(dqkv + (int64_t)r * p.ldq + k0, v, n, p.scale); });
   // dK[r][k] = scale * sum_i dS[i][r] Q[i][k]
   attn_products<4, 4>(Tn, d, Tn, [&](int r, int i) { return sG[i * ls + r]; },
-                      [&](int k, int i) { return TT<T>::to_f(sQ[i * ld + k]); },
+                      [&](int k, int i) { return sQ[i * ld + k]; },
                       [&](int r, int k0, const float* v, int n) {
-                        attn_put4<T>(dqkv + (int64_t)r * p.ldq + d + k0, v, n, p.scale);
+                        attn_put4(dqkv + (int64_t)r * p.ldq + d + k0, v, n, p.scale);
                       });
   // dV[r][k] = sum_i P[i][r] dA[i][k]
   attn_products<4, 4>(Tn, d, Tn, [&](int r, int i) { return sP[i * ls + r]; },
-                      [&](int k, int i) { return TT<T>::to_f(sD[i * ld + k]); },
+                      [&](int k, int i) { return sD[i * ld + k]; },
                       [&](int r, int k0, const float* v, int n) {
-                        attn_put4<T>(dqkv + (int64_t)r * p.ldq + 2 * d + k0, v, n, 1.f);
+                        attn_put4(dqkv + (int64_t)r * p.ldq + 2 * d + k0, v, n, 1.f);
                       });
 }
 
@@ -3817,9 +3804,9 @@ hipError_t launch_attn(bool bf16, bool bwd, const AttnProb* probs, const int32_t
   static const hipError_t attr = [] {
     hipError_t e = hipSuccess, r;
     const void* k[4] = {reinterpret_cast<const void*>(&attn_fwd_mfma_kernel),
-                        reinterpret_cast<const void*>(&attn_fwd_kernel<float>),
+                        reinterpret_cast<const void*>(&attn_fwd_kernel),
                         reinterpret_cast<const void*>(&attn_bwd_mfma_kernel),
-                        reinterpret_cast<const void*>(&attn_bwd_kernel<float>)};
+                        reinterpret_cast<const void*>(&attn_bwd_kernel)};
     for (const void* f : k) {
       r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
       if (r != hipSuccess) e = r;
@@ -3831,12 +3818,12 @@ hipError_t launch_attn(bool bf16, bool bwd, const AttnProb* probs, const int32_t
     if (bf16)
       hipLaunchKernelGGL(attn_bwd_mfma_kernel, dim3(nblocks), dim3(256), lds_bytes, s, probs, tile_map);
     else
-      hipLaunchKernelGGL(attn_bwd_kernel<float>, dim3(nblocks), dim3(256), lds_bytes, s, probs, tile_map);
+      hipLaunchKernelGGL(attn_bwd_kernel, dim3(nblocks), dim3(256), lds_bytes, s, probs, tile_map);
   } else {
     if (bf16)
       hipLaunchKernelGGL(attn_fwd_mfma_kernel, dim3(nblocks), dim3(256), lds_bytes, s, probs, tile_map);
     else
-      hipLaunchKernelGGL(attn_fwd_kernel<float>, dim3(nblocks), dim3(256), lds_bytes, s, probs, tile_map);
+      hipLaunchKernelGGL(attn_fwd_kernel, dim3(nblocks), dim3(256), lds_bytes, s, probs, tile_map);
   }
   return hipGetLastError();
 }
