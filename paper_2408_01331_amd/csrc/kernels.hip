@@ -939,7 +939,7 @@ __device__ __forceinline__ void microtile_of(int t, int& rg, int& pg) {
 
 // Weight-gradient operands of one k-block (BK output pixels), both written to
 // LDS as [row][pixel], for channel counts that are no whole 16-byte vectors
-// (models whose channels cannot be stored padded): threads 0..127 build A,
+// (a model too large to pad, a narrow last conv): threads 0..127 build A,
 // rows = output channel o, from dZ (the pooled gradient G[w][o], already
 // ReLU'-masked, and the window argmax); threads 128..255 build B, rows = j =
 // (u, v, c) plus the bias column j == KH*KW*C reading 1, from the input patch
@@ -2587,9 +2587,10 @@ void conv_halo_kernel(const ConvProb* __restrict__ probs, const int32_t* __restr
   }
 }
 
-// Halo-tiled pass of a launch whose tiles leave CUs idle (HALO_SMALL_MAX): small
-// tiles of four waves, bf16 64x64 or 128x32, fp32 32x32 or 64x16. The order of k is that
-// of the other shapes, so results do not depend on the choice.
+// Halo-tiled pass of a short launch, or of one that large tiles would fill badly
+// (the planner's HALO_SMALL_*): small tiles of four waves, bf16 64x64 or 128x32,
+// fp32 32x32 or 64x16. The order of k is that of the other shapes, so results do
+// not depend on the choice.
 template <typename T, bool DGRAD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 void conv_halo_small_kernel(const ConvProb* __restrict__ probs, const int32_t* __restrict__ tile_map) {

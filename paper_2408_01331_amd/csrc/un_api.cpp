@@ -1574,7 +1574,10 @@ static void build_tables(un_ctx* c, Tables& T) {
       // vector of it at a time (ldwt and tap * O are multiples of it too), in
       // launches large enough to fill the chip with an eighth of the threads:
       // the 3.1 M elements of cifar16 52 -> 42 us (step 1154 -> 1145), resnet8's
-      // 0.77 M 19.1 -> 18.3; the 30 k of 7 models on 3 datasets lost 5 us
+      // 0.77 M 19.1 -> 18.3; the 30 k of 7 models on 3 datasets lost 5 us. A line
+      // at 2^16 / 2^18 / 2^19 / 2^20 elements is within 1 % on 43 CNN hybrids but
+      // for 8 bf16 and fp32 models of three 24-channel convs (0.09 M): 151 / 148 /
+      // 148 / 148 and 330 / 323 / 322 / 322 us per step
       const int vec = bf ? 8 : 4;
       rp[k].rows = elems >= 1 << 19 && rp[k].WT && rp[k].O % vec == 0 && rp[k].ldwt % vec == 0 ? vec : 1;
       const int nb = cdiv((int64_t)(rp[k].O / rp[k].rows) * (rp[k].J + 1), REDUCE_BLOCK);
@@ -1954,8 +1957,9 @@ static un_status plan_and_alloc(un_ctx* c, bool dry = false) {
   // --- allocate the arena: buffers + tables (room for the tables of any
   // active subset: never larger than twice the full set's, except that a
   // launch of few enough tiles for the small tiles may come out of a full one
-  // with large tiles: at most 4 x GEMM_SMALL_MAX_F32 entries, 4.3 times that with
-  // the XCD padding (one run of 8 among 7 of 1), 8 bytes each)
+  // with large tiles: at most 4 x GEMM_SMALL_MAX_F32 entries (bf16: 2 x
+  // GEMM_SMALL_BWD), 4.3 times that with the XCD padding (one run of 8 among 7 of
+  // 1), 8 bytes each)
   // The same goes for the halo conv launches: at most the small tiles of all.
   size_t halo_small = 0;
   for (auto& m : c->models)
